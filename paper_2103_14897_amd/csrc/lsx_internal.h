@@ -168,6 +168,8 @@ hipError_t launch_phase_table(hipStream_t s, int64_t N, const double* K2, double
 hipError_t launch_phase_apply(hipStream_t s, int64_t N, int W, const double2* ph, double2* c);
 hipError_t launch_pass(hipStream_t s, int fmt, int W, int ntiles, int nb, int ksplit, const PassArgs& a,
                        bool batched = false);
+// row-split tiles (lsx_rowsplit.hip): ms waves on consecutive row blocks of 16 nb columns
+hipError_t launch_rowsplit(hipStream_t s, int fmt, int ntiles, int nb, int ms, const PassArgs& a);
 // Batched launches with a.persist set: computes (once per kernel) the persistent grid of the pass
 // kernel launch_pass would use, launching nothing, so no occupancy query runs under capture.
 hipError_t prepare_persistent(int fmt, int W, int nb, int ksplit, const PassArgs& a);
