@@ -22,6 +22,16 @@ void set_error(const std::string& msg);
     }                                                                                       \
   } while (0)
 
+// Launch bounds of the kernels with matrix instructions.  Left to itself the compiler gives a
+// workgroup of up to four waves the whole register file (512 per lane), selects the matrix
+// instructions' accumulation-register form and then copies every accumulator to and from the
+// ordinary registers around each loop pass.  Asking for two waves per SIMD caps a lane at 256
+// registers, which selects the form that accumulates in ordinary registers, with no copies:
+// a loop of six independent FP64 accumulator chains ran at 32.5 TF with them and at 67.6 TF
+// without at one wave per SIMD, 47.8 and 77.7 TF at four.  `cap` is false for the shapes whose
+// accumulators and operands do not fit 256 registers (they would spill in the loop).
+#define LSX_MFMA_BOUNDS(threads, cap) __launch_bounds__(threads, (cap) ? 2 : 1)
+
 // ---------------------------------------------------------------- storage formats
 // Propagator storage, per fibre f of length L (all formats zero-padded):
 //  PF_F64    : complex128 P, Lp = roundup(L,16); chunk (rb, ks) = rows 16rb.., cols 4ks..

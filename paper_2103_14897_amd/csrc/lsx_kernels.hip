@@ -174,14 +174,14 @@ __device__ __forceinline__ void k_pass_f64_tile(const PassArgs& a0, int ti, doub
 }
 
 template <int NB, int KS, int U, bool GATHER, bool BATCH>
-__global__ __launch_bounds__(64 * KS) void k_pass_f64(PassArgs a0) {
+__global__ LSX_MFMA_BOUNDS(64 * KS, NB < 4) void k_pass_f64(PassArgs a0) {
   extern __shared__ double red[];
   if (a0.tcount && (int)blockIdx.x >= *a0.tcount) return;
   k_pass_f64_tile<NB, KS, U, GATHER, BATCH>(a0, blockIdx.x, red);
 }
 
 template <int NB, int KS, int U, bool GATHER>
-__global__ __launch_bounds__(64 * KS) void k_pass_f64_persist(PassArgs a0) {
+__global__ LSX_MFMA_BOUNDS(64 * KS, NB < 4) void k_pass_f64_persist(PassArgs a0) {
   extern __shared__ double red[];
   persistent_tiles(a0, [&](int ti) { k_pass_f64_tile<NB, KS, U, GATHER, true>(a0, ti, red); });
 }
@@ -233,14 +233,14 @@ __device__ __forceinline__ void k_pass_f32_tile(const PassArgs& a0, int ti, doub
 }
 
 template <int NB, int KS, int U, bool GATHER, bool BATCH>
-__global__ __launch_bounds__(64 * KS) void k_pass_f32(PassArgs a0) {
+__global__ LSX_MFMA_BOUNDS(64 * KS, NB * U < 16) void k_pass_f32(PassArgs a0) {
   extern __shared__ double red[];
   if (a0.tcount && (int)blockIdx.x >= *a0.tcount) return;
   k_pass_f32_tile<NB, KS, U, GATHER, BATCH>(a0, blockIdx.x, red);
 }
 
 template <int NB, int KS, int U, bool GATHER>
-__global__ __launch_bounds__(64 * KS) void k_pass_f32_persist(PassArgs a0) {
+__global__ LSX_MFMA_BOUNDS(64 * KS, NB * U < 16) void k_pass_f32_persist(PassArgs a0) {
   extern __shared__ double red[];
   persistent_tiles(a0, [&](int ti) { k_pass_f32_tile<NB, KS, U, GATHER, true>(a0, ti, red); });
 }
@@ -342,14 +342,14 @@ __device__ __forceinline__ void k_pass_bf16x3_tile(const PassArgs& a0, int ti, d
 }
 
 template <int NB, int KS, int U, bool GATHER, bool BATCH>
-__global__ __launch_bounds__(64 * KS) void k_pass_bf16x3(PassArgs a0) {
+__global__ LSX_MFMA_BOUNDS(64 * KS, NB == 1) void k_pass_bf16x3(PassArgs a0) {
   extern __shared__ double red[];
   if (a0.tcount && (int)blockIdx.x >= *a0.tcount) return;
   k_pass_bf16x3_tile<NB, KS, U, GATHER, BATCH>(a0, blockIdx.x, red);
 }
 
 template <int NB, int KS, int U, bool GATHER>
-__global__ __launch_bounds__(64 * KS) void k_pass_bf16x3_persist(PassArgs a0) {
+__global__ LSX_MFMA_BOUNDS(64 * KS, NB == 1) void k_pass_bf16x3_persist(PassArgs a0) {
   extern __shared__ double red[];
   persistent_tiles(a0, [&](int ti) { k_pass_bf16x3_tile<NB, KS, U, GATHER, true>(a0, ti, red); });
 }

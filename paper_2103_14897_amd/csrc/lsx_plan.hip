@@ -329,7 +329,7 @@ __global__ __launch_bounds__(256) void k_bj_pairs(BJArgs g) {
 // A[l % 16][l / 16] and B as B[l / 16][l % 16] of a 16x4 / 4x16 step and leaves C[4 r + l / 16]
 // [l % 16] in element r, so the accumulators of X = A_t Q_P' are, element for element, the B
 // operands of the second product Q_P^T X.
-__global__ __launch_bounds__(256) void k_bj_tiles(BJArgs g, int total) {
+__global__ LSX_MFMA_BOUNDS(256, true) void k_bj_tiles(BJArgs g, int total) {
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int item = blockIdx.x * 4 + wv;
   if (item >= total) return;

@@ -40,7 +40,7 @@ __device__ __forceinline__ void stage_load_f32(double2 (&v)[PER], const PassArgs
 }
 
 template <int NB, int MS, bool GATHER>
-__global__ __launch_bounds__(64 * MS) void k_pass_f32m(PassArgs a) {
+__global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f32m(PassArgs a) {
   using SM = StageMap<NB, MS>;
   constexpr int KC = SM::KC;
   __shared__ float4 xs[2][SM::CR][SM::CW];
@@ -168,7 +168,7 @@ struct StageBF {
 };
 
 template <int NB, int MS, bool GATHER>
-__global__ __launch_bounds__(64 * MS) void k_pass_bf16m(PassArgs a) {
+__global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_bf16m(PassArgs a) {
   constexpr int CW = StageBF<NB>::CW, KP = StageBF<NB>::KP;
   constexpr int PER = 32 * CW / (64 * MS), RSTEP = 64 * MS / CW;
   __shared__ __attribute__((aligned(16))) unsigned short xb[2][6][CW][KP];

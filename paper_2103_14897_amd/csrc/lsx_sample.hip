@@ -409,7 +409,7 @@ __device__ __forceinline__ void mlp_hidden(const float* sp, const MlpOff& o, int
   }
 }
 
-__global__ __launch_bounds__(256) void k_mlp_fwd(const float* theta, int nin, const float* X, int64_t M, float* z) {
+__global__ LSX_MFMA_BOUNDS(256, true) void k_mlp_fwd(const float* theta, int nin, const float* X, int64_t M, float* z) {
   extern __shared__ float sp[];
   const MlpOff o(nin);
   mlp_stage(theta, o.n, sp);
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const float* theta, int nin, co
 //   grad W1 = X^T d1, b1, b2, w3, b3: sums over rows.
 // Each wave stages its chunk's H1, d2 (then d1) and inputs in its own LDS tiles; the waves'
 // sums are added in wave order at the end and the workgroup writes partial[blockIdx.x][:].
-__global__ __launch_bounds__(256) void k_mlp_bwd(const float* theta, int nin, const float* X, int64_t M,
+__global__ LSX_MFMA_BOUNDS(256, true) void k_mlp_bwd(const float* theta, int nin, const float* X, int64_t M,
                                                  const float* dz, const double* gscale, float* partial) {
   extern __shared__ float sp[];
   const MlpOff o(nin);
