@@ -677,6 +677,11 @@ struct lsx_plan {
   int nsym = 0;        // point symmetries the propagators are shared over (identity excluded)
   DBuf<double2> zero;  // 1 KiB of zeros (out-of-range operand loads of the passes)
   LayerDev L[kMaxLayers];
+  // energy: one term per pair of opposite potential coefficients of every layer, and the
+  // coefficient at index zero
+  DBuf<EnergyTerm> eterm;
+  int neterm = 0;
+  double v0 = 0.0;
   int nstates = 0;
   int max_w = 0;  // states with more wavepackets are refused (0: no limit)
 };
@@ -1195,6 +1200,40 @@ static lsx_status precompute_layer(lsx_plan* pl, int layer, hipStream_t s) {
   return LSX_OK;
 }
 
+// The potential terms of the energy (see EnergyTerm): pairs of opposite coefficients as one term,
+// a coefficient without a partner (negligible, see build_stencil) by itself.
+static lsx_status energy_terms(lsx_plan* pl, hipStream_t s) {
+  const lsx_system* sys = pl->sys;
+  std::vector<EnergyTerm> t;
+  for (int j = 0; j < sys->nl; ++j) {
+    const Stencil& S = sys->pot[j];
+    const int d = sys->ldim[j];
+    for (int p = 0; p < S.nv; ++p) {
+      int q = 0;  // partner: the coefficient at the opposite index
+      for (; q < S.nv; ++q) {
+        bool opposite = true;
+        for (int k = 0; k < d; ++k) opposite = opposite && S.idx[(size_t)q * d + k] == -S.idx[(size_t)p * d + k];
+        if (opposite) break;
+      }
+      if (q == p) {
+        pl->v0 += S.re[p];
+      } else if (q == S.nv) {
+        t.push_back({pl->L[j].nbr.p, S.nv, p, make_double2(S.re[p], S.im[p])});
+      } else if (p < q) {
+        t.push_back({pl->L[j].nbr.p, S.nv, p, make_double2(S.re[p] + S.re[q], S.im[p] - S.im[q])});
+      }
+    }
+  }
+  if (!t.empty())
+    while (t.size() % kEnergyTermGroup != 0) {
+      EnergyTerm e = t[0];  // a term of value zero
+      e.v = make_double2(0.0, 0.0);
+      t.push_back(e);
+    }
+  pl->neterm = (int)t.size();
+  return pl->eterm.upload(t, s);
+}
+
 // band_req: 0 the default tolerance for the precision (LSX_BAND_TOL overrides it), < 0 dense
 // products, > 0 that tolerance.
 static lsx_status plan_create(lsx_system* sys, double tau, int32_t scheme, double kappa, int32_t precision,
@@ -1253,6 +1292,7 @@ static lsx_status plan_create(lsx_system* sys, double tau, int32_t scheme, doubl
     for (int p = 0; p < sys->pot[j].nv; ++p) v[p] = make_double2(sys->pot[j].re[p], sys->pot[j].im[p]);
     if ((st = ld.v.upload(v, s)) != LSX_OK) return cleanup(st);
   }
+  if ((st = energy_terms(pl, s)) != LSX_OK) return cleanup(st);
   {
     // position tables between the layers' orders and the canonical order; a layer whose order
     // is the canonical one (the last layer, unless point symmetries reorder it) needs none
@@ -1934,7 +1974,7 @@ extern "C" lsx_status lsx_state_create(lsx_plan* pl, int32_t W, void* dev_ptr, l
   // observables: mass, energy and the fibre masses of every layer in one result block
   size_t nfsum = 0;
   for (int j = 0; j < pl->sys->nl; ++j) nfsum += (size_t)pl->L[j].nf;
-  if ((e = st->partial.alloc((size_t)st->nred * W)) != LSX_OK) return cleanup(e);
+  if ((e = st->partial.alloc((size_t)2 * st->nred * W)) != LSX_OK) return cleanup(e);
   if ((e = st->result.alloc((size_t)W * (2 + std::max<size_t>(nfsum, 1)))) != LSX_OK) return cleanup(e);
   if (hipDeviceSynchronize() != hipSuccess) return cleanup(fail(LSX_E_HIP, "state setup failed"));
   pl->nstates++;
@@ -2337,6 +2377,37 @@ extern "C" lsx_status lsx_phase(lsx_plan* pl, lsx_state* st, int32_t half, void*
   return r.phase(half);
 }
 
+// Mass and / or energy of the columns of c into out[0 .. W) and the following W doubles (`count`
+// receives how many), through nred partial sums per column: one sweep for both where `room`
+// doubles hold two sets of partials, else one after the other (the same sums either way).
+static hipError_t reduce_columns(const lsx_plan* pl, hipStream_t s, int W, const double2* c, uint32_t mask,
+                                 double* partial, int nred, size_t room, double* out, size_t& count) {
+  ReduceArgs a;
+  a.N = pl->sys->N;
+  a.W = W;
+  a.c = c;
+  a.zero = pl->zero.p;
+  a.K2 = pl->K2.p;
+  a.terms = pl->eterm.p;
+  a.nterms = pl->neterm;
+  a.v0 = pl->v0;
+  const size_t set = (size_t)nred * W;
+  double* mass = (mask & LSX_OBS_MASS) ? out : nullptr;
+  double* energy = (mask & LSX_OBS_ENERGY) ? out + (mass ? W : 0) : nullptr;
+  count = (size_t)(mass ? W : 0) + (energy ? W : 0);
+  a.pmass = a.penergy = partial;
+  if (mass && energy) {
+    if (2 * set <= room) {
+      a.penergy = partial + set;
+    } else {
+      const hipError_t e = launch_reduce(s, a, nred, mass, nullptr);
+      if (e != hipSuccess) return e;
+      mass = nullptr;
+    }
+  }
+  return launch_reduce(s, a, nred, mass, energy);
+}
+
 extern "C" lsx_status lsx_observables(lsx_plan* pl, lsx_state* st, uint32_t mask, double* out, void* stream) {
   LSX_TRY(check_pair(pl, st));
   if (!out) return fail(LSX_E_INVALID, "null output");
@@ -2348,18 +2419,7 @@ extern "C" lsx_status lsx_observables(lsx_plan* pl, lsx_state* st, uint32_t mask
   const int64_t N = sys->N;
   double* dres = st->result.p;
   size_t count = 0;
-  if (mask & LSX_OBS_MASS) {
-    LSX_HIP_TRY(launch_reduce(s, 0, N, W, st->buf[0], pl->K2.p, 0, nullptr, nullptr, 0, nullptr, nullptr, 0,
-                              nullptr, nullptr, st->partial.p, st->nred, dres + count));
-    count += W;
-  }
-  if (mask & LSX_OBS_ENERGY) {
-    const int nv3 = sys->nl > 2 ? sys->pot[2].nv : 0;
-    LSX_HIP_TRY(launch_reduce(s, 1, N, W, st->buf[0], pl->K2.p, sys->pot[0].nv, pl->L[0].nbr.p, pl->L[0].v.p,
-                              sys->pot[1].nv, pl->L[1].nbr.p, pl->L[1].v.p, nv3, pl->L[2].nbr.p, pl->L[2].v.p,
-                              st->partial.p, st->nred, dres + count));
-    count += W;
-  }
+  LSX_HIP_TRY(reduce_columns(pl, s, W, st->buf[0], mask, st->partial.p, st->nred, st->partial.n, dres, count));
   const uint32_t fm_bit[kMaxLayers] = {LSX_OBS_FIBRE_MASS_1, LSX_OBS_FIBRE_MASS_2, LSX_OBS_FIBRE_MASS_3};
   for (int layer = 1; layer <= sys->nl; ++layer)
     if (mask & fm_bit[layer - 1]) {
@@ -2400,18 +2460,7 @@ extern "C" lsx_status lsx_observables_noalloc(lsx_plan* pl, const void* dev_c, i
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const double2* c = static_cast<const double2*>(dev_c);
   size_t count = 0;
-  if (mask & LSX_OBS_MASS) {
-    LSX_HIP_TRY(launch_reduce(s, 0, N, W, c, pl->K2.p, 0, nullptr, nullptr, 0, nullptr, nullptr, 0, nullptr,
-                              nullptr, part, nred, dev_out + count));
-    count += W;
-  }
-  if (mask & LSX_OBS_ENERGY) {
-    const int nv3 = sys->nl > 2 ? sys->pot[2].nv : 0;
-    LSX_HIP_TRY(launch_reduce(s, 1, N, W, c, pl->K2.p, sys->pot[0].nv, pl->L[0].nbr.p, pl->L[0].v.p,
-                              sys->pot[1].nv, pl->L[1].nbr.p, pl->L[1].v.p, nv3, pl->L[2].nbr.p, pl->L[2].v.p, part,
-                              nred, dev_out + count));
-    count += W;
-  }
+  LSX_HIP_TRY(reduce_columns(pl, s, W, c, mask, part, nred, (size_t)kStaticScratchDoubles, dev_out, count));
   const uint32_t fm_bit[kMaxLayers] = {LSX_OBS_FIBRE_MASS_1, LSX_OBS_FIBRE_MASS_2, LSX_OBS_FIBRE_MASS_3};
   for (int layer = 1; layer <= sys->nl; ++layer)
     if (mask & fm_bit[layer - 1]) {

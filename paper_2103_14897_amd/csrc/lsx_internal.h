@@ -183,10 +183,31 @@ hipError_t launch_rowsplit(hipStream_t s, int fmt, int ntiles, int nb, int ms, c
 // Batched launches with a.persist set: computes (once per kernel) the persistent grid of the pass
 // kernel launch_pass would use, launching nothing, so no occupancy query runs under capture.
 hipError_t prepare_persistent(int fmt, int W, int nb, int ksplit, const PassArgs& a);
-hipError_t launch_reduce(hipStream_t s, int kind, int64_t N, int W, const double2* c, const double* K2, int nv1,
-                         const int32_t* nbr1, const double2* v1, int nv2, const int32_t* nbr2, const double2* v2,
-                         int nv3, const int32_t* nbr3, const double2* v3, double* partial, int nblocks,
-                         double* out);
+// One term of the energy's potential part: neighbour nbr[i * nv + col] of row i with value v (the
+// coefficient plus the conjugate of its partner at the opposite index)
+struct EnergyTerm {
+  const int32_t* nbr;
+  int32_t nv, col;
+  double2 v;
+};
+constexpr int kEnergyTermGroup = 6;  // the term lists are padded to a multiple of this
+// Mass and energy of every column: partial sums of nblocks workgroups into pmass / penergy
+// ([nblocks][W] each), then the sums into mass / energy (either null: not computed).  v0: the
+// potentials' coefficient at index zero.
+struct ReduceArgs {
+  int64_t N = 0;
+  int W = 0;
+  int CW = 0;  // columns per sweep (set by the launcher)
+  const double2* c = nullptr;
+  const double2* zero = nullptr;
+  const double* K2 = nullptr;
+  const EnergyTerm* terms = nullptr;
+  int nterms = 0;
+  double v0 = 0.0;
+  double* pmass = nullptr;
+  double* penergy = nullptr;
+};
+hipError_t launch_reduce(hipStream_t s, const ReduceArgs& a, int nblocks, double* mass, double* energy);
 hipError_t launch_fibre_mass(hipStream_t s, int nf, const int32_t* ptr, const int32_t* rows, int W,
                              const double2* c, double* out);
 // Device address of this GPU's static scratch array (kStaticScratchDoubles doubles), looked up

@@ -35,75 +35,100 @@ __global__ __launch_bounds__(256) void k_phase_apply(int64_t N, int W, int TW, c
 }
 
 // ---------------------------------------------------------------- FP64 reductions
-// kind 0: |c|^2;  kind 1: 1/2 K2 |c|^2 + Re conj(c_iw) sum_p v_p c_{nbr(i,p), w} (both layers)
-__global__ __launch_bounds__(256) void k_reduce_partial(int kind, int64_t N, int W, const double2* c,
-                                                        const double* K2, int nv1, const int32_t* nbr1,
-                                                        const double2* v1, int nv2, const int32_t* nbr2,
-                                                        const double2* v2, int nv3, const int32_t* nbr3,
-                                                        const double2* v3, double* partial, int R) {
-  __shared__ double red[256];
-  const int b = blockIdx.x;
-  const int64_t i0 = (int64_t)b * R;
-  const int64_t i1 = min(N, i0 + R);
-  const int WB = W < 256 ? W : 256;
-  const int S = 256 / WB;
-  const int tid = threadIdx.x;
-  for (int w0 = 0; w0 < W; w0 += WB) {
-    const int w = w0 + tid % WB, s = tid / WB;
-    double acc = 0.0;
-    if (w < W && s < S) {
-      for (int64_t i = i0 + s; i < i1; i += S) {
-        const double2 x = c[i * W + w];
-        const double m2 = x.x * x.x + x.y * x.y;
-        if (kind == 0) {
-          acc += m2;
-        } else {
-          double hr = 0.0, hi = 0.0;
-          for (int p = 0; p < nv1; ++p) {
-            const int j = nbr1[i * nv1 + p];
-            if (j >= 0) {
-              const double2 y = c[(int64_t)j * W + w], v = v1[p];
-              hr += v.x * y.x - v.y * y.y;
-              hi += v.x * y.y + v.y * y.x;
-            }
+// Mass sum_i |c_iw|^2 and energy sum_i 1/2 |K_i|^2 |c_iw|^2 + Re conj(c_iw) (V c)_iw of every
+// column, as partial sums of one workgroup's rows.  V is Hermitian, so the terms of a coefficient
+// and of its partner at the opposite index have equal real parts once summed over the rows: one
+// term per pair (EnergyTerm) reads half the neighbours of the stencil.
+//
+// Bound by the neighbour reads: each row is read again by every term, the first layers' from far
+// away.  As in the semi-implicit step, XCD x (workgroup b runs on XCD b % 8) takes the contiguous
+// slab x of the rows and sweeps it in blocks of CW columns, so that those reads hit its L2; a
+// thread loads the indices, then the values, of up to kTermsPerLoad terms together.  Twisted
+// bilayer, N = 398821, W = 128: mass and energy 2.48 ms as separate sweeps of whole rows over all
+// twelve neighbours, 0.76 ms as one sweep over six (mass alone 0.19 ms both ways).
+constexpr int kReduceThreads = 512;
+constexpr int kTermsPerLoad = kEnergyTermGroup;
+template <bool MASS, bool ENERGY>
+__global__ __launch_bounds__(kReduceThreads) void k_reduce_partial(ReduceArgs a) {
+  __shared__ double red[2][kReduceThreads / 64][64];
+  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int nx = (int)gridDim.x >= 64 ? 8 : 1;  // a small grid takes one slab
+  const int x = b % nx, lb = b / nx;
+  const int G = ((int)gridDim.x - x + nx - 1) / nx;  // workgroups of this slab
+  const int64_t slab = (a.N + nx - 1) / nx;
+  const int64_t r0 = x * slab, r1 = min(a.N, r0 + slab);
+  const int rpi = kReduceThreads / a.CW;
+  const int tr = threadIdx.x / a.CW, tc = threadIdx.x - tr * a.CW;
+  const int W = a.W;
+  for (int cb = 0; cb < W; cb += a.CW) {
+    const int w = cb + tc;
+    const bool ok = w < W;
+    double am = 0.0, ae = 0.0;
+    for (int64_t i = r0 + (int64_t)lb * rpi + tr; ok && i < r1; i += (int64_t)G * rpi) {
+      const double2 c = a.c[i * W + w];
+      const double m2 = c.x * c.x + c.y * c.y;
+      if (MASS) am += m2;
+      if (ENERGY) {
+        double hr = 0.0, hi = 0.0;
+        for (int t0 = 0; t0 < a.nterms; t0 += kTermsPerLoad) {
+          int32_t j[kTermsPerLoad];
+          double2 y[kTermsPerLoad];
+#pragma unroll
+          for (int t = 0; t < kTermsPerLoad; ++t) {
+            const EnergyTerm e = a.terms[t0 + t];  // the list is padded to whole groups
+            j[t] = e.nbr[i * e.nv + e.col];
           }
-          for (int p = 0; p < nv2; ++p) {
-            const int j = nbr2[i * nv2 + p];
-            if (j >= 0) {
-              const double2 y = c[(int64_t)j * W + w], v = v2[p];
-              hr += v.x * y.x - v.y * y.y;
-              hi += v.x * y.y + v.y * y.x;
-            }
+#pragma unroll
+          for (int t = 0; t < kTermsPerLoad; ++t) y[t] = *(j[t] >= 0 ? a.c + (int64_t)j[t] * W + w : a.zero);
+#pragma unroll
+          for (int t = 0; t < kTermsPerLoad; ++t) {
+            const double2 v = a.terms[t0 + t].v;
+            hr += v.x * y[t].x - v.y * y[t].y;
+            hi += v.x * y[t].y + v.y * y[t].x;
           }
-          for (int p = 0; p < nv3; ++p) {
-            const int j = nbr3[i * nv3 + p];
-            if (j >= 0) {
-              const double2 y = c[(int64_t)j * W + w], v = v3[p];
-              hr += v.x * y.x - v.y * y.y;
-              hi += v.x * y.y + v.y * y.x;
-            }
-          }
-          acc += 0.5 * K2[i] * m2 + (x.x * hr + x.y * hi);
         }
+        ae += (0.5 * a.K2[i] + a.v0) * m2 + (c.x * hr + c.y * hi);
       }
     }
-    red[tid] = acc;
+    // sum over the rows of a column: lanes CW apart, then the waves in order
+    for (int o = a.CW; o < 64; o <<= 1) {
+      if (MASS) am += __shfl_xor(am, o);
+      if (ENERGY) ae += __shfl_xor(ae, o);
+    }
+    if (lane < a.CW) {
+      red[0][wave][lane] = am;
+      red[1][wave][lane] = ae;
+    }
     __syncthreads();
-    if (tid < WB && w0 + tid < W) {
-      double sum = 0.0;
-      for (int j = 0; j < S; ++j) sum += red[j * WB + tid];
-      partial[(int64_t)b * W + w0 + tid] = sum;
+    const int tw = threadIdx.x;
+    if (tw < a.CW && cb + tw < W) {
+      double sm = 0.0, se = 0.0;
+      for (int k = 0; k < kReduceThreads / 64; ++k) {
+        sm += red[0][k][tw];
+        se += red[1][k][tw];
+      }
+      if (MASS) a.pmass[(int64_t)b * W + cb + tw] = sm;
+      if (ENERGY) a.penergy[(int64_t)b * W + cb + tw] = se;
     }
     __syncthreads();
   }
 }
 
-__global__ void k_reduce_final(int nblocks, int W, const double* partial, double* out) {
-  const int w = blockIdx.x * blockDim.x + threadIdx.x;
-  if (w < W) {
-    double s = 0.0;
-    for (int b = 0; b < nblocks; ++b) s += partial[(int64_t)b * W + w];
-    out[w] = s;
+// out[w] = sum over the workgroups of partial[b][w]: eight columns per workgroup, 32 threads
+// per column each taking every 32nd partial, then a fixed-order sum
+__global__ __launch_bounds__(256) void k_reduce_final(int nblocks, int W, const double* partial, double* out) {
+  __shared__ double red[32][8];
+  const int tc = threadIdx.x & 7, tr = threadIdx.x >> 3;
+  const int w = blockIdx.x * 8 + tc;
+  double s = 0.0;
+  if (w < W)
+    for (int b = tr; b < nblocks; b += 32) s += partial[(int64_t)b * W + w];
+  red[tr][tc] = s;
+  __syncthreads();
+  if (tr == 0 && w < W) {
+    double t = 0.0;
+    for (int k = 0; k < 32; ++k) t += red[k][tc];
+    out[w] = t;
   }
 }
 
@@ -163,17 +188,29 @@ hipError_t launch_phase_apply(hipStream_t s, int64_t N, int W, const double2* ph
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(hipStream_t s, int kind, int64_t N, int W, const double2* c, const double* K2, int nv1,
-                         const int32_t* nbr1, const double2* v1, int nv2, const int32_t* nbr2, const double2* v2,
-                         int nv3, const int32_t* nbr3, const double2* v3, double* partial, int nblocks,
-                         double* out) {
-  const int R = (int)((N + nblocks - 1) / nblocks);
-  hipLaunchKernelGGL(k_reduce_partial, dim3(nblocks), dim3(256), 0, s, kind, N, W, c, K2, nv1, nbr1, v1, nv2,
-                     nbr2, v2, nv3, nbr3, v3, partial, R);
+hipError_t launch_reduce(hipStream_t s, const ReduceArgs& a0, int nblocks, double* mass, double* energy) {
+  if (!mass && !energy) return hipSuccess;
+  ReduceArgs a = a0;
+  a.CW = 8;
+  while (a.CW > 1 && a.CW / 2 >= a.W) a.CW /= 2;  // narrow states: no idle lanes beyond W
+  const dim3 grid(nblocks), block(kReduceThreads);
+  if (mass && energy)
+    hipLaunchKernelGGL((k_reduce_partial<true, true>), grid, block, 0, s, a);
+  else if (mass)
+    hipLaunchKernelGGL((k_reduce_partial<true, false>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_reduce_partial<false, true>), grid, block, 0, s, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_reduce_final, dim3((W + 255) / 256), dim3(256), 0, s, nblocks, W, partial, out);
-  return hipGetLastError();
+  const dim3 fgrid((a.W + 7) / 8);
+  if (e == hipSuccess && mass) {
+    hipLaunchKernelGGL(k_reduce_final, fgrid, dim3(256), 0, s, nblocks, a.W, a.pmass, mass);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess && energy) {
+    hipLaunchKernelGGL(k_reduce_final, fgrid, dim3(256), 0, s, nblocks, a.W, a.penergy, energy);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 hipError_t launch_fibre_mass(hipStream_t s, int nf, const int32_t* ptr, const int32_t* rows, int W,
