@@ -677,6 +677,9 @@ struct lsx_plan {
   int nsym = 0;        // point symmetries the propagators are shared over (identity excluded)
   DBuf<double2> zero;  // 1 KiB of zeros (out-of-range operand loads of the passes)
   LayerDev L[kMaxLayers];
+  // row parts of the kernels that read potential neighbours, and their row list
+  Sweep sweep;
+  DBuf<int32_t> sweep_rows;
   // energy: one term per pair of opposite potential coefficients of every layer, and the
   // coefficient at index zero
   DBuf<EnergyTerm> eterm;
@@ -1234,6 +1237,39 @@ static lsx_status energy_terms(lsx_plan* pl, hipStream_t s) {
   return pl->eterm.upload(t, s);
 }
 
+// Row parts of the neighbour-reading kernels (Sweep).  Up to kSweepMinRows rows a part of the
+// canonical order fits an XCD's L2 as it is (8 columns of 32768 rows are 4 MB); beyond, the layer-1
+// fibres are cut into eight ranges of about equal rows.  Two lattices only: with a third index
+// block a range of layer-1 fibres keeps fewer of the other layers' neighbours together (energy of
+// the twisted trilayer, N = 415135, W = 100: 1.26 ms, 1.11 in canonical order; Example 3, N = 74037:
+// 0.37 and 0.30).
+static constexpr int64_t kSweepMinRows = 32768;
+static lsx_status build_sweep(lsx_plan* pl, hipStream_t s) {
+  const lsx_system* sys = pl->sys;
+  const int64_t N = sys->N;
+  for (int x = 0; x <= 8; ++x) pl->sweep.start[x] = (int32_t)std::min(N, x * ((N + 7) / 8));
+  if (N <= kSweepMinRows || sys->nl != 2 || !sys->standard) return LSX_OK;
+  const FibreTable& ft = sys->fib[0];
+  std::vector<uint8_t> part((size_t)N);
+  int64_t count[9] = {};
+  for (size_t f = 0; f + 1 < ft.ptr.size(); ++f) {
+    const int x = (int)std::min<int64_t>(7, (int64_t)ft.ptr[f] * 8 / N);
+    for (int a = ft.ptr[f]; a < ft.ptr[f + 1]; ++a) part[ft.rows[a]] = (uint8_t)x;
+    count[x + 1] += ft.ptr[f + 1] - ft.ptr[f];
+  }
+  int32_t at[8];
+  for (int x = 0; x < 8; ++x) {
+    pl->sweep.start[x] = at[x] = (int32_t)count[x];
+    count[x + 1] += count[x];
+  }
+  pl->sweep.start[8] = (int32_t)N;
+  std::vector<int32_t> order((size_t)N);
+  for (int64_t i = 0; i < N; ++i) order[at[part[i]]++] = (int32_t)i;
+  LSX_TRY(pl->sweep_rows.upload(order, s));
+  pl->sweep.order = pl->sweep_rows.p;
+  return LSX_OK;
+}
+
 // band_req: 0 the default tolerance for the precision (LSX_BAND_TOL overrides it), < 0 dense
 // products, > 0 that tolerance.
 static lsx_status plan_create(lsx_system* sys, double tau, int32_t scheme, double kappa, int32_t precision,
@@ -1293,6 +1329,7 @@ static lsx_status plan_create(lsx_system* sys, double tau, int32_t scheme, doubl
     if ((st = ld.v.upload(v, s)) != LSX_OK) return cleanup(st);
   }
   if ((st = energy_terms(pl, s)) != LSX_OK) return cleanup(st);
+  if ((st = build_sweep(pl, s)) != LSX_OK) return cleanup(st);
   {
     // position tables between the layers' orders and the canonical order; a layer whose order
     // is the canonical one (the last layer, unless point symmetries reorder it) needs none
@@ -2383,7 +2420,7 @@ extern "C" lsx_status lsx_phase(lsx_plan* pl, lsx_state* st, int32_t half, void*
 static hipError_t reduce_columns(const lsx_plan* pl, hipStream_t s, int W, const double2* c, uint32_t mask,
                                  double* partial, int nred, size_t room, double* out, size_t& count) {
   ReduceArgs a;
-  a.N = pl->sys->N;
+  a.sweep = pl->sweep;
   a.W = W;
   a.c = c;
   a.zero = pl->zero.p;
@@ -3280,16 +3317,15 @@ lsx_status phase_canon(lsx_plan* pl, lsx_state* st, int half, hipStream_t s) {
   return LSX_OK;
 }
 
-// Alg. 1 / Alg. 4 step from buf[0] into buf[1], then back into buf[0]
-lsx_status si_once(lsx_plan* pl, lsx_state* st, const double* wt1, const int32_t* fid1, const double* wt2,
-                   const int32_t* fid2, hipStream_t s) {
+// Alg. 1 / Alg. 4 step from the runner's current array into the other one
+lsx_status si_once(Runner& r, const double* wt1, const int32_t* fid1, const double* wt2, const int32_t* fid2) {
+  lsx_plan* pl = r.pl;
   const lsx_system* sys = pl->sys;
-  LSX_HIP_TRY(launch_si_step(s, sys->N, st->W, pl->tau, pl->K2.p, sys->pot[0].nv, pl->L[0].nbr.p, pl->L[0].v.p,
-                             wt1, fid1, sys->pot[1].nv, pl->L[1].nbr.p, pl->L[1].v.p, wt2, fid2, st->buf[0],
-                             st->buf[1], pl->zero.p));
-  Runner r{pl, st, s};
-  r.cur = 1;
-  return r.finish();
+  LSX_HIP_TRY(launch_si_step(r.s, pl->sweep, r.st->W, pl->tau, pl->K2.p, sys->pot[0].nv, pl->L[0].nbr.p, pl->L[0].v.p,
+                             wt1, fid1, sys->pot[1].nv, pl->L[1].nbr.p, pl->L[1].v.p, wt2, fid2, r.st->buf[r.cur],
+                             r.st->buf[1 - r.cur], pl->zero.p));
+  r.cur ^= 1;
+  return LSX_OK;
 }
 }  // namespace
 
@@ -3299,8 +3335,11 @@ extern "C" lsx_status lsx_si_step(lsx_plan* pl, lsx_state* st, int64_t nsteps, v
   if (pl->sys->nl != 2 || !pl->sys->standard)
     return fail(LSX_E_INVALID, "the semi-implicit step takes two-layer systems built from lattices");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  for (int64_t k = 0; k < nsteps && pl->sys->N > 0; ++k) LSX_TRY(si_once(pl, st, nullptr, nullptr, nullptr, nullptr, s));
-  return LSX_OK;
+  if (pl->sys->N == 0) return LSX_OK;
+  return run_passes(pl, st, s, [&](Runner& r) -> lsx_status {
+    for (int64_t k = 0; k < nsteps; ++k) LSX_TRY(si_once(r, nullptr, nullptr, nullptr, nullptr));
+    return LSX_OK;
+  });
 }
 
 extern "C" lsx_status lsx_rb_step(lsx_sampler* sm, const double* u, int64_t nsteps, void* stream) {
@@ -3313,12 +3352,14 @@ extern "C" lsx_status lsx_rb_step(lsx_sampler* sm, const double* u, int64_t nste
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const int W = sm->st->W, pmax = std::max(sm->p[0], sm->p[1]);
   const int64_t per = (int64_t)W * pmax;
-  for (int64_t k = 0; k < nsteps; ++k) {
-    for (int j = 0; j < 2; ++j)
-      LSX_HIP_TRY(launch_subset_weights(s, sm->nf[j], W, sm->p[j], pmax, u + (2 * k + j) * per, sm->wt[j].p));
-    LSX_TRY(si_once(sm->pl, sm->st, sm->wt[0].p, sm->fid[0].p, sm->wt[1].p, sm->fid[1].p, s));
-  }
-  return LSX_OK;
+  return run_passes(sm->pl, sm->st, s, [&](Runner& r) -> lsx_status {
+    for (int64_t k = 0; k < nsteps; ++k) {
+      for (int j = 0; j < 2; ++j)
+        LSX_HIP_TRY(launch_subset_weights(s, sm->nf[j], W, sm->p[j], pmax, u + (2 * k + j) * per, sm->wt[j].p));
+      LSX_TRY(si_once(r, sm->wt[0].p, sm->fid[0].p, sm->wt[1].p, sm->fid[1].p));
+    }
+    return LSX_OK;
+  });
 }
 
 extern "C" lsx_status lsx_ss_step(lsx_sampler* sm, const double* u, int64_t nsteps, void* stream) {

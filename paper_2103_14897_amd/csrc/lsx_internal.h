@@ -183,6 +183,18 @@ hipError_t launch_rowsplit(hipStream_t s, int fmt, int ntiles, int nb, int ms, c
 // Batched launches with a.persist set: computes (once per kernel) the persistent grid of the pass
 // kernel launch_pass would use, launching nothing, so no occupancy query runs under capture.
 hipError_t prepare_persistent(int fmt, int W, int nb, int ksplit, const PassArgs& a);
+// The rows as eight parts, part x = positions [start[x], start[x + 1]) of the row list `order` (null:
+// the canonical order): the kernels that read every row's potential neighbours let XCD x sweep part
+// x, kSweepCW columns at a time.  A part holds the rows of a range of layer-1 fibres, in canonical
+// order, so that the layer-1 neighbours, up to tens of thousands of rows away, lie in the same
+// part, and the rows between a neighbour's first and last use are an eighth of what a contiguous
+// slab of the canonical order would have between them: they fit the XCD's 4 MB of L2.
+struct Sweep {
+  const int32_t* order = nullptr;
+  int32_t start[9] = {};
+};
+constexpr int kSweepCW = 32;
+
 // One term of the energy's potential part: neighbour nbr[i * nv + col] of row i with value v (the
 // coefficient plus the conjugate of its partner at the opposite index)
 struct EnergyTerm {
@@ -195,7 +207,7 @@ constexpr int kEnergyTermGroup = 6;  // the term lists are padded to a multiple 
 // ([nblocks][W] each), then the sums into mass / energy (either null: not computed).  v0: the
 // potentials' coefficient at index zero.
 struct ReduceArgs {
-  int64_t N = 0;
+  Sweep sweep;
   int W = 0;
   int CW = 0;  // columns per sweep (set by the launcher)
   const double2* c = nullptr;
@@ -217,7 +229,7 @@ constexpr int kMaxDevices = 64;
 hipError_t static_scratch(double** ptr);
 
 // ---------------------------------------------------------------- stochastic steps (lsx_sample.hip)
-hipError_t launch_si_step(hipStream_t s, int64_t N, int W, double tau, const double* K2, int nv1,
+hipError_t launch_si_step(hipStream_t s, const Sweep& sweep, int W, double tau, const double* K2, int nv1,
                           const int32_t* nbr1, const double2* v1, const double* wt1, const int32_t* fid1, int nv2,
                           const int32_t* nbr2, const double2* v2, const double* wt2, const int32_t* fid2,
                           const double2* X, double2* Y, const double2* zero);

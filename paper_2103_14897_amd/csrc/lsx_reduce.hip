@@ -41,22 +41,21 @@ __global__ __launch_bounds__(256) void k_phase_apply(int64_t N, int W, int TW, c
 // term per pair (EnergyTerm) reads half the neighbours of the stencil.
 //
 // Bound by the neighbour reads: each row is read again by every term, the first layers' from far
-// away.  As in the semi-implicit step, XCD x (workgroup b runs on XCD b % 8) takes the contiguous
-// slab x of the rows and sweeps it in blocks of CW columns, so that those reads hit its L2; a
+// away.  As in the semi-implicit step, XCD x (workgroup b runs on XCD b % 8) takes part x of the
+// rows (Sweep) and sweeps it in blocks of CW columns, so that those reads hit its L2; a
 // thread loads the indices, then the values, of up to kTermsPerLoad terms together.  Twisted
 // bilayer, N = 398821, W = 128: mass and energy 2.48 ms as separate sweeps of whole rows over all
-// twelve neighbours, 0.76 ms as one sweep over six (mass alone 0.19 ms both ways).
+// twelve neighbours, 0.73 ms as one sweep over six (mass alone 0.19 ms both ways).
 constexpr int kReduceThreads = 512;
 constexpr int kTermsPerLoad = kEnergyTermGroup;
 template <bool MASS, bool ENERGY>
 __global__ __launch_bounds__(kReduceThreads) void k_reduce_partial(ReduceArgs a) {
   __shared__ double red[2][kReduceThreads / 64][64];
   const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nx = (int)gridDim.x >= 64 ? 8 : 1;  // a small grid takes one slab
+  const int nx = (int)gridDim.x >= 64 ? 8 : 1;  // a small grid takes the parts as one
   const int x = b % nx, lb = b / nx;
-  const int G = ((int)gridDim.x - x + nx - 1) / nx;  // workgroups of this slab
-  const int64_t slab = (a.N + nx - 1) / nx;
-  const int64_t r0 = x * slab, r1 = min(a.N, r0 + slab);
+  const int G = ((int)gridDim.x - x + nx - 1) / nx;  // workgroups of this part
+  const int r0 = nx == 8 ? a.sweep.start[x] : 0, r1 = nx == 8 ? a.sweep.start[x + 1] : a.sweep.start[8];
   const int rpi = kReduceThreads / a.CW;
   const int tr = threadIdx.x / a.CW, tc = threadIdx.x - tr * a.CW;
   const int W = a.W;
@@ -64,7 +63,8 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce_partial(ReduceArgs a)
     const int w = cb + tc;
     const bool ok = w < W;
     double am = 0.0, ae = 0.0;
-    for (int64_t i = r0 + (int64_t)lb * rpi + tr; ok && i < r1; i += (int64_t)G * rpi) {
+    for (int k = r0 + lb * rpi + tr; ok && k < r1; k += G * rpi) {
+      const int64_t i = a.sweep.order ? a.sweep.order[k] : k;
       const double2 c = a.c[i * W + w];
       const double m2 = c.x * c.x + c.y * c.y;
       if (MASS) am += m2;
@@ -191,7 +191,7 @@ hipError_t launch_phase_apply(hipStream_t s, int64_t N, int W, const double2* ph
 hipError_t launch_reduce(hipStream_t s, const ReduceArgs& a0, int nblocks, double* mass, double* energy) {
   if (!mass && !energy) return hipSuccess;
   ReduceArgs a = a0;
-  a.CW = 8;
+  a.CW = a.sweep.order ? kSweepCW : 8;
   while (a.CW > 1 && a.CW / 2 >= a.W) a.CW /= 2;  // narrow states: no idle lanes beyond W
   const dim3 grid(nblocks), block(kReduceThreads);
   if (mass && energy)

@@ -20,8 +20,12 @@ namespace lsx {
 //
 // Cache blocking: every neighbour row is read again by nv other rows, the layer-1 ones
 // (m - p, n) from far away in canonical order.  Workgroup b runs on XCD b % 8, so XCD x
-// takes the contiguous slab x of the rows, and sweeps it in blocks of CW columns: the rows
-// between a neighbour's first and last use then fit in that XCD's own L2.
+// takes part x of the rows (Sweep), and sweeps it in blocks of CW columns: the rows
+// between a neighbour's first and last use then fit in that XCD's own L2, which the output of a
+// large state does not displace (non-temporal stores).  Twisted bilayer, N = 398821, W = 128: 0.93
+// ms a step in contiguous slabs with 8-column sweeps and ordinary stores, 0.87 ms now, 1.9 of 4.9
+// TB/s of state read and written once; L2 read misses (34 to 22 million lines) bound it.
+// Measured and not used: the next row's indices loaded ahead of the current row's values (0.98 ms).
 //
 // Stencil sizes NV1, NV2 are compile-time for the common cases (1D cosine: 2, 2D first shell:
 // 6) so every neighbour index and value is loaded before any is used; a missing neighbour
@@ -54,7 +58,7 @@ __device__ __forceinline__ void si_stencil(int64_t i, int w, int W, int nv, cons
 }
 
 template <int NV1, int NV2>
-__global__ __launch_bounds__(256) void k_si_step(int64_t N, int W, int CW, double tau, const double* __restrict__ K2,
+__global__ __launch_bounds__(256) void k_si_step(Sweep sweep, int W, int CW, double tau, const double* __restrict__ K2,
                                                  int nv1, const int32_t* __restrict__ nbr1,
                                                  const double2* __restrict__ v1, const double* __restrict__ wt1,
                                                  const int32_t* __restrict__ fid1, int nv2,
@@ -64,14 +68,14 @@ __global__ __launch_bounds__(256) void k_si_step(int64_t N, int W, int CW, doubl
                                                  const double2* __restrict__ zero) {
   const int xcd = blockIdx.x & 7;
   const int G = gridDim.x >> 3, lb = blockIdx.x >> 3;
-  const int64_t slab = (N + 7) / 8;
-  const int64_t r0 = xcd * slab, r1 = min(N, r0 + slab);
+  const int r0 = sweep.start[xcd], r1 = sweep.start[xcd + 1];
   const int rpi = 256 / CW;  // rows per workgroup iteration
   const int tr = threadIdx.x / CW, tc = threadIdx.x - tr * CW;
   for (int cb = 0; cb < W; cb += CW) {
     const int w = cb + tc;
     if (w >= W) continue;
-    for (int64_t i = r0 + (int64_t)lb * rpi + tr; i < r1; i += (int64_t)G * rpi) {
+    for (int k = r0 + lb * rpi + tr; k < r1; k += G * rpi) {
+      const int64_t i = sweep.order ? sweep.order[k] : k;
       double s1r = 0.0, s1i = 0.0, s2r = 0.0, s2i = 0.0;
       si_stencil<NV1>(i, w, W, nv1, nbr1, v1, X, zero, s1r, s1i);
       si_stencil<NV2>(i, w, W, nv2, nbr2, v2, X, zero, s2r, s2i);
@@ -84,7 +88,15 @@ __global__ __launch_bounds__(256) void k_si_step(int64_t N, int W, int CW, doubl
       // z / (1 + i b) = z (1 - i b) / (1 + b^2)
       const double b = 0.5 * tau * K2[i];
       const double den = 1.0 + b * b;
-      Y[i * W + w] = make_double2((zr + b * zi) / den, (zi - b * zr) / den);
+      const double2 out = make_double2((zr + b * zi) / den, (zi - b * zr) / den);
+      if (sweep.order) {  // empty compiler barriers keep the two branches' stores apart
+        asm volatile("" ::: "memory");
+        __builtin_nontemporal_store(out.x, &Y[i * W + w].x);
+        __builtin_nontemporal_store(out.y, &Y[i * W + w].y);
+        asm volatile("" ::: "memory");
+      } else {
+        Y[i * W + w] = out;
+      }
     }
   }
 }
@@ -707,30 +719,31 @@ static unsigned grid_for(int64_t n, int64_t cap) {
   return (unsigned)(g < 1 ? 1 : (g > cap ? cap : g));
 }
 
-hipError_t launch_si_step(hipStream_t s, int64_t N, int W, double tau, const double* K2, int nv1,
+hipError_t launch_si_step(hipStream_t s, const Sweep& sweep, int W, double tau, const double* K2, int nv1,
                           const int32_t* nbr1, const double2* v1, const double* wt1, const int32_t* fid1, int nv2,
                           const int32_t* nbr2, const double2* v2, const double* wt2, const int32_t* fid2,
                           const double2* X, double2* Y, const double2* zero) {
-  if (N == 0) return hipSuccess;
-  // column block: LSX_SI_CW (1..256, a power of two) or 8; 256 workgroups per XCD
+  if (sweep.start[8] == 0) return hipSuccess;
+  // column block: LSX_SI_CW (1..256, a power of two) or the sweep's; 256 workgroups per XCD
   static const int cw_env = [] {
     const char* v = std::getenv("LSX_SI_CW");
-    const int x = v ? std::atoi(v) : 8;
-    return (x >= 1 && x <= 256 && (x & (x - 1)) == 0) ? x : 8;
+    const int x = v ? std::atoi(v) : 0;
+    return (x >= 1 && x <= 256 && (x & (x - 1)) == 0) ? x : 0;
   }();
-  int CW = cw_env;
+  int CW = cw_env ? cw_env : sweep.order ? kSweepCW : 8;
   while (CW > 1 && CW / 2 >= W) CW /= 2;  // narrow states: no idle lanes beyond W
-  const int64_t rows_per_xcd = (N + 7) / 8;
+  int64_t rows_per_xcd = 0;
+  for (int x = 0; x < 8; ++x) rows_per_xcd = std::max<int64_t>(rows_per_xcd, sweep.start[x + 1] - sweep.start[x]);
   const int64_t G = std::min<int64_t>(256, std::max<int64_t>(1, (rows_per_xcd * CW + 255) / 256));
   const dim3 grid((unsigned)(8 * G));
   if (nv1 == 2 && nv2 == 2)
-    hipLaunchKernelGGL((k_si_step<2, 2>), grid, dim3(256), 0, s, N, W, CW, tau, K2, nv1, nbr1, v1, wt1, fid1, nv2,
+    hipLaunchKernelGGL((k_si_step<2, 2>), grid, dim3(256), 0, s, sweep, W, CW, tau, K2, nv1, nbr1, v1, wt1, fid1, nv2,
                        nbr2, v2, wt2, fid2, X, Y, zero);
   else if (nv1 == 6 && nv2 == 6)
-    hipLaunchKernelGGL((k_si_step<6, 6>), grid, dim3(256), 0, s, N, W, CW, tau, K2, nv1, nbr1, v1, wt1, fid1, nv2,
+    hipLaunchKernelGGL((k_si_step<6, 6>), grid, dim3(256), 0, s, sweep, W, CW, tau, K2, nv1, nbr1, v1, wt1, fid1, nv2,
                        nbr2, v2, wt2, fid2, X, Y, zero);
   else
-    hipLaunchKernelGGL((k_si_step<0, 0>), grid, dim3(256), 0, s, N, W, CW, tau, K2, nv1, nbr1, v1, wt1, fid1, nv2,
+    hipLaunchKernelGGL((k_si_step<0, 0>), grid, dim3(256), 0, s, sweep, W, CW, tau, K2, nv1, nbr1, v1, wt1, fid1, nv2,
                        nbr2, v2, wt2, fid2, X, Y, zero);
   return hipGetLastError();
 }
