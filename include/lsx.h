@@ -328,7 +328,9 @@ lsx_status lsx_state_device_ptr(const lsx_state* st, void** dev_ptr);
  * workgroup covers 16*nb columns and either 16 output rows with ks > 0 waves splitting the
  * fibre length, or (ks = -2, -4 or -8, mixed paths) -ks consecutive 16-row blocks, one per wave,
  * that share the state operand staged once per workgroup in LDS (each wave multiplies only its
- * own row block's band, see lsx_plan_band; FP32 needs -ks <= 4 nb, BF16x3 nb <= 2).  For W = 1
+ * own row block's band, see lsx_plan_band; FP32 needs -ks <= 4 nb, BF16x3 nb <= 2).  LSX_FP64
+ * shapes with ks = 4 and nb <= 2 work the same way, four row blocks to a workgroup, on layers
+ * where that makes at least 1024 workgroups.  For W = 1
  * (matrix-vector passes) ks < 0 means 64 output rows, one per lane, with -ks waves splitting
  * the fibre length, and nb = 8 tiles that multiply the fibres sharing a
  * stored propagator together (lsx_state_set_tuning).  At creation every candidate shape is

@@ -613,6 +613,7 @@ struct LayerDev {
   std::vector<int32_t> h_d0;    // fibre position of each fibre's diagonal (its representative's)
   std::vector<int32_t> rep;     // distinct-propagator slot of each fibre
   int nunique = 0;
+  int64_t row_groups4 = 0;  // groups of four 16-row blocks over the layer's fibres
   // The plan's order of the layer's rows (fibre position -> canonical index): the system's
   // fibres with their rows ascending, except that a fibre sharing its representative's
   // propagator through a point symmetry lists the images of the representative's rows.
@@ -1321,6 +1322,7 @@ static lsx_status plan_create(lsx_system* sys, double tau, int32_t scheme, doubl
     ld.nf = (int)ft.ptr.size() - 1;
     ld.maxL = ft.maxL;
     ld.h_ptr = ft.ptr;
+    for (int f = 0; f < ld.nf; ++f) ld.row_groups4 += (ft.ptr[f + 1] - ft.ptr[f] + 63) / 64;
     if ((st = ld.ptr.upload(ft.ptr, s)) != LSX_OK) return cleanup(st);
     if ((st = ld.rows.upload(ld.h_rows, s)) != LSX_OK) return cleanup(st);
     if ((st = ld.nbr.upload(sys->nbr[j], s)) != LSX_OK) return cleanup(st);
@@ -1603,6 +1605,20 @@ static bool use_step_graphs(const float* tuned_us, int nl) {
 }
 
 
+// The kernel behind the tile shape (nb, ks) of a layer's passes, as launch_pass takes it: ks, or
+// -4 for FP64 shapes of four waves that take consecutive row blocks and share the staged state
+// (the row-split kernel) instead of splitting the fibre length.  The row split is the faster use of
+// four waves once its workgroups, a quarter as many, still fill the chip: kRowsplitMinTiles is four
+// of them per CU.  Step times, K-split / row split with one column block: twisted bilayer
+// Ec 800, W = 32 (300 workgroups) 17.0 / 20.4 us, W = 128 (1200) 38.8 / 33.5; Ec 2000, W = 32 (1600)
+// 78.8 / 68.1; chain Ec 2e4, W = 64 (410) 17.6 / 21.1, Ec 9.7e4 (2300) 45.0 / 43.1; twisted Ec 6500,
+// W = 128: 4640 / 3790.
+static constexpr int64_t kRowsplitMinTiles = 1024;
+static int pass_waves(const lsx_plan* pl, int layer, int W, int nb, int ks) {
+  if (pl->fmt != PF_F64 || W == 1 || ks != 4 || nb > 2) return ks;
+  return pl->L[layer - 1].row_groups4 * ((W + 16 * nb - 1) / (16 * nb)) >= kRowsplitMinTiles ? -4 : ks;
+}
+
 // Tile order of one fibre pass.  Workgroup i of a launch runs on XCD i % 8, and each XCD has
 // its own L2, so fibres are assigned to XCDs whole (longest first, to the least-loaded XCD) and
 // the XCD queues are interleaved; every queue lists its largest tiles first.  Fibres that share
@@ -1720,9 +1736,12 @@ static lsx_status choose_cycle(lsx_plan* pl, lsx_state* st, bool tune_store) {
   };
   Opt opt[kMaxLayers][3];
   for (int l = 0; l < nl; ++l) {
-    opt[l][0] = {true, st->nb[l], st->ks[l], st->u[l], st->ntiles[l], st->tiles[l].p};
-    opt[l][1] = {st->u[l] == 1 || st->u[l] == 2, st->nb[l], st->ks[l], 3 - st->u[l], st->ntiles[l], st->tiles[l].p};
-    opt[l][2] = {st->alt_nb[l] > 0, st->alt_nb[l], st->alt_ks[l], st->alt_u[l], st->alt_ntiles[l], st->alt_tiles[l].p};
+    const int ks0 = pass_waves(pl, l + 1, W, st->nb[l], st->ks[l]);
+    const int ks2 = pass_waves(pl, l + 1, W, st->alt_nb[l], st->alt_ks[l]);
+    const bool depth = (st->u[l] == 1 || st->u[l] == 2) && ks0 > 0;
+    opt[l][0] = {true, st->nb[l], ks0, st->u[l], st->ntiles[l], st->tiles[l].p};
+    opt[l][1] = {depth, st->nb[l], ks0, 3 - st->u[l], st->ntiles[l], st->tiles[l].p};
+    opt[l][2] = {st->alt_nb[l] > 0, st->alt_nb[l], ks2, st->alt_u[l], st->alt_ntiles[l], st->alt_tiles[l].p};
   }
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
@@ -1879,10 +1898,12 @@ static lsx_status choose_tiles(lsx_plan* pl, lsx_state* st) {
         if (cands.size() > 1) continue;  // no fibre of this layer shares its propagator
         c.nb = 1;
       }
+      const int pks = pass_waves(pl, layer, W, c.nb, c.ks);
+      if (pks != c.ks && c.u == 1) continue;  // the row split has one depth
       std::vector<TileDesc> t;
       const int wt = (W == 1) ? 1 : (W + 16 * c.nb - 1) / (16 * c.nb);
       // row blocks per tile: W = 1 four for ks < 0 (one row per lane), else -ks for the row-split shapes
-      build_tiles(pl, layer, W, c.nb, 0, wt, t, c.ks < 0 ? (W == 1 ? 4 : -c.ks) : 1, W == 1 && c.nb == kOrbitNB);
+      build_tiles(pl, layer, W, c.nb, 0, wt, t, pks < 0 ? (W == 1 ? 4 : -pks) : 1, W == 1 && c.nb == kOrbitNB);
       DBuf<TileDesc> d;
       if ((err = d.upload(t, nullptr)) != LSX_OK) break;
       float ms = 0.f;
@@ -1918,7 +1939,7 @@ static lsx_status choose_tiles(lsx_plan* pl, lsx_state* st) {
         auto time_reps = [&](int reps, float& per) {
           hipError_t e = hipEventRecord(e0, nullptr);
           for (int r = 0; r < reps && e == hipSuccess; ++r)
-            e = launch_pass(nullptr, pl->fmt, W, (int)t.size(), c.nb, c.ks, a);
+            e = launch_pass(nullptr, pl->fmt, W, (int)t.size(), c.nb, pks, a);
           if (e == hipSuccess) e = hipEventRecord(e1, nullptr);
           if (e == hipSuccess) e = hipEventSynchronize(e1);
           float total = 0.f;
@@ -1926,7 +1947,7 @@ static lsx_status choose_tiles(lsx_plan* pl, lsx_state* st) {
           per = total / reps;
           return e;
         };
-        hipError_t he = launch_pass(nullptr, pl->fmt, W, (int)t.size(), c.nb, c.ks, a);
+        hipError_t he = launch_pass(nullptr, pl->fmt, W, (int)t.size(), c.nb, pks, a);
         if (he == hipSuccess) he = time_reps(2, ms);
         if (he == hipSuccess && ms < 1.0f) he = time_reps(std::min(100, std::max(5, (int)(1.0f / std::max(ms, 1e-3f)))), ms);
         if (he != hipSuccess) {
@@ -2100,7 +2121,8 @@ extern "C" lsx_status lsx_state_set_tuning(lsx_state* st, int32_t layer, int32_t
     return fail(LSX_E_INVALID, "orbit tiles need fibres that share a stored propagator");
   const int wt = (W == 1) ? 1 : (W + 16 * nb - 1) / (16 * nb);
   std::vector<TileDesc> t;
-  build_tiles(pl, layer, W, nb, 0, wt, t, ks < 0 ? (W == 1 ? 4 : -ks) : 1, orbit);
+  const int pks = pass_waves(pl, layer, W, nb, ks);
+  build_tiles(pl, layer, W, nb, 0, wt, t, pks < 0 ? (W == 1 ? 4 : -pks) : 1, orbit);
   DBuf<TileDesc> d;
   LSX_TRY(d.upload(t, nullptr));
   const int l = layer - 1;
@@ -2176,7 +2198,8 @@ struct Runner {
     a.W = st->W;
     a.nt = st->nt;
     a.u = st->u[layer - 1];
-    LSX_HIP_TRY(launch_pass(s, pl->fmt, st->W, st->ntiles[layer - 1], st->nb[layer - 1], st->ks[layer - 1], a));
+    LSX_HIP_TRY(launch_pass(s, pl->fmt, st->W, st->ntiles[layer - 1], st->nb[layer - 1],
+                            pass_waves(pl, layer, st->W, st->nb[layer - 1], st->ks[layer - 1]), a));
     cur ^= 1;
     lay = outlay;
     return LSX_OK;
@@ -3429,7 +3452,8 @@ extern "C" lsx_status lsx_sampler_increments(lsx_sampler* sm, int32_t layer, int
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   PassArgs a = canon_pass_args(pl, st, layer, half);
   a.tiles = st->tiles[layer - 1].p;
-  LSX_HIP_TRY(launch_pass(s, pl->fmt, st->W, st->ntiles[layer - 1], st->nb[layer - 1], st->ks[layer - 1], a));
+  LSX_HIP_TRY(launch_pass(s, pl->fmt, st->W, st->ntiles[layer - 1], st->nb[layer - 1],
+                          pass_waves(pl, layer, st->W, st->nb[layer - 1], st->ks[layer - 1]), a));
   LSX_HIP_TRY(launch_fibre_incr(s, ld.nf, ld.ptr.p, ld.rows.p, st->W, st->buf[0], st->buf[1], b));
   return LSX_OK;
 }

@@ -156,6 +156,144 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f32m(PassArgs a) {
   pass_epilogue<NB, 1, true, false>(a, t, acc, nullptr, wc, wok);
 }
 
+// Row-split FP64 pass: MS waves on consecutive row blocks, chunks of KC k-steps (4 KC rows) of the
+// state staged in double-buffered LDS as the three B operands of the 3M products (x_r, x_i - x_r,
+// x_r + x_i).  FP64 matrix instructions and vector instructions do not overlap on a SIMD (64
+// cycles each; four integer additions between them measured 82), so the loop is laid out to
+// have next to no vector instructions: the sums are formed once per staged element instead of
+// once per wave, propagator chunks are read at a uniform address plus the lane, each into the
+// registers its predecessor just left (a whole chunk of products ahead of its use, and no second
+// set of registers), and the chunks a wave only stages are separate loops, without a branch
+// around the products (which copied every accumulator).  Five vector instructions per 24
+// products, 92 registers (NB = 2): five waves per SIMD.
+// Twisted bilayer, N = 398821, W = 128, tau = 5e-3, layer 1 / 2: 1688 / 1515 us a pass, 59 TF of
+// matrix work; the fastest K-split shape takes 2030 / 1800, as did this kernel when it formed the
+// sums in every wave with addresses in vector registers (1970 / 1790).  Measured slower: MS = 2
+// and 8 (1890, 1744), two waves' register buffers in turn (1962), next k-step's LDS reads ahead
+// (1745: 108 registers).
+template <int NB, int MS, int KC, bool GATHER>
+__global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f64m(PassArgs a) {
+  constexpr int CW = 16 * NB, CR = 4 * KC;
+  constexpr int PER = CR * CW / (64 * MS), RSTEP = 64 * MS / CW;
+  static_assert(PER >= 1, "at least one staged element per thread");
+  __shared__ double xs[2][3][NB][CR][16];
+  const TileDesc t0 = a.tiles[blockIdx.x];
+  if (t0.f < 0) return;
+  const int r0 = t0.r0, L = t0.L;
+  const int nks = ((L + 15) & ~15) >> 2;
+  const int lane = threadIdx.x & 63, kw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  TileDesc t = t0;
+  t.rb = t0.rb * MS + kw;
+  const bool act = t.rb < ((L + 15) >> 4);
+  const double2* zp = reinterpret_cast<const double2*>(a.zero);
+  const double2* P = reinterpret_cast<const double2*>(reinterpret_cast<const char*>(a.P) + t.poff) +
+                     (int64_t)(act ? t.rb : 0) * nks * 64;
+  int wc[NB];
+  bool wok[NB];
+  tile_cols<NB>(a, t, li, wc, wok);
+  const int c = threadIdx.x % CW, rr0 = threadIdx.x / CW;
+  const int sw = t.wb * CW + c;
+  const bool sok = sw < a.W;
+  v4d k1[NB], k2[NB], k3[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) k1[nb] = k2[nb] = k3[nb] = (v4d){0.0, 0.0, 0.0, 0.0};
+  int klo, khi;  // staged chunks of CR rows: the union of the group's bands
+  tile_band(t0, 4 * nks, CR, klo, khi);
+  int wlo = klo * KC, whi = min(khi * KC, nks);  // this wave's own band in k-steps
+  if (a.rb_band && t0.bb >= 0 && act) {
+    const int2 wb = reinterpret_cast<const int2*>(a.rb_band)[t0.bb + t.rb];
+    wlo = wb.x >> 2;
+    whi = min(wb.y, 4 * nks) >> 2;
+  }
+  if (!act) whi = wlo;
+  double2 sv[PER];
+  const double2* xp = a.X + (int64_t)(r0 + rr0) * a.W + sw;  // this thread's element of chunk 0
+  auto load_state = [&](int ch) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int k = CR * ch + rr0 + j * RSTEP;
+      const bool ok = sok && k < L;
+      if (GATHER) {
+        int64_t off = xrow<GATHER>(a, r0 + (ok ? k : 0)) * a.W + sw;
+        asm volatile("" : "+v"(off));
+        sv[j] = *(ok ? a.X + off : zp);
+      } else {
+        const double2* q = xp + (int64_t)(CR * ch + j * RSTEP) * a.W;
+        sv[j] = *(ok ? q : zp);
+      }
+    }
+  };
+  const int sb = c >> 4, sc = c & 15;
+  auto store_state = [&](int buf) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      xs[buf][0][sb][rr0 + j * RSTEP][sc] = sv[j].x;
+      xs[buf][1][sb][rr0 + j * RSTEP][sc] = sv[j].y - sv[j].x;
+      xs[buf][2][sb][rr0 + j * RSTEP][sc] = sv[j].x + sv[j].y;
+    }
+  };
+  // propagator chunk of k-step ks (zeros outside the wave's band; the address is uniform)
+  auto load_p = [&](int ks) {
+    const double2* q = (ks >= wlo && ks < whi) ? P + (int64_t)ks * 64 : zp;
+    return q[(unsigned)lane];
+  };
+  // chunks this wave multiplies: [alo, ahi), inside the staged [klo, khi)
+  const int alo = act ? min(max(wlo / KC, klo), khi) : khi;
+  const int ahi = act ? min(max((whi + KC - 1) / KC, alo), khi) : khi;
+  double2 E[KC];
+  int ch = klo;
+  load_state(klo);
+  if (alo < ahi)
+#pragma unroll
+    for (int u = 0; u < KC; ++u) E[u] = load_p(KC * alo + u);
+  store_state(0);
+  __syncthreads();
+  // stage chunk ch + 1 while chunk ch is multiplied (or passed over)
+  auto next = [&](int cn) {
+    if (cn < khi) {
+      store_state((cn - klo) & 1);
+      __syncthreads();
+    }
+  };
+  for (; ch < alo; ++ch) {
+    load_state(ch + 1);
+    next(ch + 1);
+  }
+  for (; ch < ahi; ++ch) {
+    load_state(ch + 1);
+    const int buf = (ch - klo) & 1;
+#pragma unroll
+    for (int u = 0; u < KC; ++u) {
+      const double2 p = E[u];
+      const double ps = p.x + p.y;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        k1[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ps, xs[buf][0][nb][4 * u + lk][li], k1[nb], 0, 0, 0);
+        k2[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.x, xs[buf][1][nb][4 * u + lk][li], k2[nb], 0, 0, 0);
+        k3[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(p.y, xs[buf][2][nb][4 * u + lk][li], k3[nb], 0, 0, 0);
+      }
+      E[u] = load_p(KC * (ch + 1) + u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    next(ch + 1);
+  }
+  for (; ch < khi; ++ch) {
+    load_state(ch + 1);
+    next(ch + 1);
+  }
+  if (!act) return;
+  double acc[NB][2][4];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      acc[nb][0][r] = k1[nb][r] - k3[nb][r];
+      acc[nb][1][r] = k1[nb][r] + k2[nb][r];
+    }
+  pass_epilogue<NB, 1, false, true>(a, t, acc, nullptr, wc, wok);
+}
+
 // Row-split BF16x3 pass: as k_pass_f32m, with 32-row chunks.  The staging threads split each
 // state value once (x~ = fp32(x) into three bf16 terms, real and imaginary parts) into six
 // LDS planes stored column-major (a lane's 8 consecutive k values are one 16-byte read);
@@ -313,7 +451,20 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_bf16m(PassArgs a) {
 // Row-split tiles of nb column blocks and ms waves (PassArgs::in_pos null: no gather)
 hipError_t launch_rowsplit(hipStream_t s, int fmt, int ntiles, int nb, int ms, const PassArgs& a) {
   const bool gather = a.in_pos != nullptr;
-  if (fmt == PF_F64) return hipErrorInvalidValue;
+  if (fmt == PF_F64) {
+#define LSX_ROWSPLIT_F64(NB_, MS_, KC_)                                                             \
+  if (nb == NB_ && ms == MS_) {                                                                     \
+    if (gather)                                                                                     \
+      hipLaunchKernelGGL((k_pass_f64m<NB_, MS_, KC_, true>), dim3(ntiles), dim3(64 * MS_), 0, s, a);  \
+    else                                                                                            \
+      hipLaunchKernelGGL((k_pass_f64m<NB_, MS_, KC_, false>), dim3(ntiles), dim3(64 * MS_), 0, s, a); \
+    return hipGetLastError();                                                                       \
+  }
+    LSX_ROWSPLIT_F64(1, 4, 4)
+    LSX_ROWSPLIT_F64(2, 4, 4)
+#undef LSX_ROWSPLIT_F64
+    return hipErrorInvalidValue;
+  }
   if (fmt == PF_BF16X3) {
 #define LSX_ROWSPLIT_BF(NB_, MS_)                                                                       \
   if (nb == NB_ && ms == MS_) {                                                                    \
