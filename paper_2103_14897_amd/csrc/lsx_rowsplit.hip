@@ -4,6 +4,16 @@
 
 namespace lsx {
 
+// State element at byte offset `off` from X, or a zero: both as one load from a selected offset
+// (`zoff`: the zero buffer's distance from X), so that no branch surrounds the load
+__device__ __forceinline__ double2 load_or_zero(const double2* X, bool ok, int64_t off, int64_t zoff) {
+  const int64_t o = ok ? off : zoff;
+  return *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(X) + o);
+}
+__device__ __forceinline__ int64_t byte_distance(const void* from, const void* to) {
+  return (int64_t)(reinterpret_cast<uintptr_t>(to) - reinterpret_cast<uintptr_t>(from));
+}
+
 // ---------------------------------------------------------------- row-split passes, LDS-staged state
 // Workgroup = MS waves on MS consecutive 16-row blocks of one fibre (tile rb counts groups
 // of MS blocks) and the same 16 NB columns.  The state operand of every 16-row chunk of
@@ -17,6 +27,12 @@ namespace lsx {
 // With band-limited products the staged chunks cover the union of the group's bands, and
 // each wave multiplies only the chunks of its own row block's band (PassArgs::rb_band), so
 // larger groups read the state operand fewer times without adding products.
+// Vector instructions take issue time from the matrix ones (32 cycles each, about 1.7 more per
+// vector instruction between them), so the propagator chunks are read at a uniform address plus
+// the lane, each into the registers its predecessor just left.  Twisted bilayer, N = 398821,
+// W = 128, tau = 1e-3, 2 column blocks and 8 waves, layer 1 / 2: 945 / 843 us a pass with a second
+// register set and addresses in vector registers, 779 / 691 now; Example 3, W = 100, best shape,
+// 447 to 390 us a step.
 template <int NB, int MS>
 struct StageMap {
   static constexpr int KC = MS >= 4 ? 8 : 4;   // k-steps per chunk
@@ -28,14 +44,17 @@ struct StageMap {
 
 template <int PER, int RSTEP, int CR, bool GATHER>
 __device__ __forceinline__ void stage_load_f32(double2 (&v)[PER], const PassArgs& a, int ch, int r0, int L, int w,
-                                               bool wok, int rr0) {
-  const double2* zx = reinterpret_cast<const double2*>(a.zero);
+                                               bool wok, int rr0, int64_t zoff) {
+  // the thread's element of the chunk's first rows, and rows RSTEP apart from there
+  const int64_t row_bytes = (int64_t)a.W * 16;
+  const int64_t off0 = (int64_t)(r0 + CR * ch + rr0) * row_bytes + (int64_t)w * 16;
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int k = CR * ch + rr0 + j * RSTEP;
     const bool ok = wok && k < L;
-    const int64_t row = xrow<GATHER>(a, r0 + (ok ? k : 0));
-    v[j] = *(ok ? a.X + row * a.W + w : zx);
+    const int64_t off = GATHER ? xrow<GATHER>(a, r0 + (ok ? k : 0)) * row_bytes + (int64_t)w * 16
+                               : off0 + (int64_t)(j * RSTEP) * row_bytes;
+    v[j] = load_or_zero(a.X, ok, off, zoff);
   }
 }
 
@@ -60,7 +79,7 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f32m(PassArgs a) {
   const bool act = t.rb < ((L + 15) >> 4);
   const float2* zp = reinterpret_cast<const float2*>(a.zero);
   const float2* P = reinterpret_cast<const float2*>(reinterpret_cast<const char*>(a.P) + t.poff) +
-                    (int64_t)(act ? t.rb : 0) * nks * 64 + lane;
+                    (int64_t)(act ? t.rb : 0) * nks * 64;
   int wc[NB];
   bool wok[NB];
   tile_cols<NB>(a, t, li, wc, wok);
@@ -78,7 +97,8 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f32m(PassArgs a) {
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) k1[nb] = k2[nb] = k3[nb] = (v4f){0.f, 0.f, 0.f, 0.f};
   double2 sv[SM::PER];
-  float2 Ac[KC], An[KC];
+  float2 E[KC];
+  const int64_t zoff = byte_distance(a.X, a.zero);
   // chunks of the band in the order c0, c0 + 1, ... (cyclically), with the workgroup's own
   // rows last: the epilogue's FP64 reload of those rows then finds them in this XCD's L2,
   // just staged
@@ -92,56 +112,53 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f32m(PassArgs a) {
     whi = (min(wb.y, 4 * nks) + SM::CR - 1) / SM::CR;
   }
   auto mine = [&](int cc) { return act && cc >= wlo && cc < whi; };
-  stage_load_f32<SM::PER, SM::RSTEP, SM::CR, GATHER>(sv, a, chunk(0), r0, L, sw, sok, rr0);
+  // propagator chunk of k-step ks (zeros outside the wave's band): a uniform address and the lane
+  auto load_p = [&](bool in, int ks) {
+    const float2* q = (in && ks < nks) ? P + (int64_t)ks * 64 : zp;
+    return q[(unsigned)lane];
+  };
+  stage_load_f32<SM::PER, SM::RSTEP, SM::CR, GATHER>(sv, a, chunk(0), r0, L, sw, sok, rr0, zoff);
   {
     const bool in = mine(chunk(0));
 #pragma unroll
-    for (int u = 0; u < KC; ++u) {
-      const int ks = KC * chunk(0) + u;
-      Ac[u] = (in && ks < nks) ? P[(int64_t)ks * 64] : *zp;
-    }
+    for (int u = 0; u < KC; ++u) E[u] = load_p(in, KC * chunk(0) + u);
   }
+  auto stage_store = [&](int buf) {
 #pragma unroll
-  for (int j = 0; j < SM::PER; ++j) {
-    const float xr = (float)sv[j].x, xi = (float)sv[j].y;
-    xs[0][rr0 + j * SM::RSTEP][c] = make_float4(xr, xi - xr, xr + xi, 0.f);
-  }
+    for (int j = 0; j < SM::PER; ++j) {
+      const float xr = (float)sv[j].x, xi = (float)sv[j].y;
+      xs[buf][rr0 + j * SM::RSTEP][c] = make_float4(xr, xi - xr, xr + xi, 0.f);
+    }
+  };
+  stage_store(0);
   __syncthreads();
   for (int ch = 0; ch < nch; ++ch) {
     const int buf = ch & 1;
-    const bool more = ch + 1 < nch;
-    if (more) {
-      stage_load_f32<SM::PER, SM::RSTEP, SM::CR, GATHER>(sv, a, chunk(ch + 1), r0, L, sw, sok, rr0);
-      const bool in = mine(chunk(ch + 1));
-#pragma unroll
-      for (int u = 0; u < KC; ++u) {
-        const int ks = KC * chunk(ch + 1) + u;
-        An[u] = (in && ks < nks) ? P[(int64_t)ks * 64] : *zp;
-      }
-    }
+    const int cn = ch + 1 < nch ? chunk(ch + 1) : 0;
+    const bool more = ch + 1 < nch, in = more && mine(cn);
+    if (more) stage_load_f32<SM::PER, SM::RSTEP, SM::CR, GATHER>(sv, a, cn, r0, L, sw, sok, rr0, zoff);
     __builtin_amdgcn_sched_barrier(0);
     if (mine(chunk(ch))) {
 #pragma unroll
       for (int u = 0; u < KC; ++u) {
-        const float ps = Ac[u].x + Ac[u].y;
+        const float2 p = E[u];
+        const float ps = p.x + p.y;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
           const float4 b = xs[buf][4 * u + lk][nb * 16 + li];
           k1[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ps, b.x, k1[nb], 0, 0, 0);
-          k2[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(Ac[u].x, b.y, k2[nb], 0, 0, 0);
-          k3[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(Ac[u].y, b.z, k3[nb], 0, 0, 0);
+          k2[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(p.x, b.y, k2[nb], 0, 0, 0);
+          k3[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(p.y, b.z, k3[nb], 0, 0, 0);
         }
+        // the next chunk's entries into the registers these products have just read
+        E[u] = load_p(in, KC * cn + u);
+        __builtin_amdgcn_sched_barrier(0);
       }
-    }
-    if (more) {
+    } else {
 #pragma unroll
-      for (int j = 0; j < SM::PER; ++j) {
-        const float xr = (float)sv[j].x, xi = (float)sv[j].y;
-        xs[buf ^ 1][rr0 + j * SM::RSTEP][c] = make_float4(xr, xi - xr, xr + xi, 0.f);
-      }
-#pragma unroll
-      for (int u = 0; u < KC; ++u) Ac[u] = An[u];
+      for (int u = 0; u < KC; ++u) E[u] = load_p(in, KC * cn + u);
     }
+    if (more) stage_store(buf ^ 1);
     __syncthreads();
   }
   if (!act) return;
@@ -208,21 +225,18 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f64m(PassArgs a) {
   }
   if (!act) whi = wlo;
   double2 sv[PER];
-  const double2* xp = a.X + (int64_t)(r0 + rr0) * a.W + sw;  // this thread's element of chunk 0
+  // this thread's element of the chunk that load_state reads next (chunks in order from klo)
+  const double2* xp = a.X + (int64_t)(r0 + CR * klo + rr0) * a.W + sw;
+  const int64_t step = (int64_t)CR * a.W;
   auto load_state = [&](int ch) {
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
       const int k = CR * ch + rr0 + j * RSTEP;
       const bool ok = sok && k < L;
-      if (GATHER) {
-        int64_t off = xrow<GATHER>(a, r0 + (ok ? k : 0)) * a.W + sw;
-        asm volatile("" : "+v"(off));
-        sv[j] = *(ok ? a.X + off : zp);
-      } else {
-        const double2* q = xp + (int64_t)(CR * ch + j * RSTEP) * a.W;
-        sv[j] = *(ok ? q : zp);
-      }
+      const double2* q = GATHER ? a.X + xrow<GATHER>(a, r0 + (ok ? k : 0)) * a.W + sw : xp + (int64_t)(j * RSTEP) * a.W;
+      sv[j] = *(ok ? q : zp);
     }
+    xp += step;
   };
   const int sb = c >> 4, sc = c & 15;
   auto store_state = [&](int buf) {
@@ -296,20 +310,20 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f64m(PassArgs a) {
 
 // Row-split BF16x3 pass: as k_pass_f32m, with 32-row chunks.  The staging threads split each
 // state value once (x~ = fp32(x) into three bf16 terms, real and imaginary parts) into six
-// LDS planes stored column-major (a lane's 8 consecutive k values are one 16-byte read);
-// every wave multiplies its own propagator rows (six bf16 planes, one chunk ahead in
-// registers) with the shared planes.  Needs MS <= 8 NB.
-template <int NB>
-struct StageBF {
-  static constexpr int CW = 16 * NB;
-  static constexpr int KP = 40;  // padded k stride of a column (32 used)
-};
-
+// LDS planes in B-operand order (lane = column + 16 (k / 8), element k % 8: a lane's operand is one
+// 16-byte read, a wave's 1 KiB in a row), two rows of a column at a time where a thread has two;
+// every wave multiplies its own propagator rows (six bf16 planes in registers) with the shared
+// planes.  Needs MS <= 8 NB.
+// Twisted bilayer, N = 398821, W = 128, tau = 1e-3, 2 column blocks and 8 waves, layer 1 / 2: 718 /
+// 651 us a pass with planes for two chunks in registers (124), their addresses in vector
+// registers and two-byte staging stores into padded columns (28% of the cycles lost to bank
+// conflicts); 690 / 624 now, with 100 registers; the trilayer's best shape 564 to 505 us.
 template <int NB, int MS, bool GATHER>
 __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_bf16m(PassArgs a) {
-  constexpr int CW = StageBF<NB>::CW, KP = StageBF<NB>::KP;
+  constexpr int CW = 16 * NB;
   constexpr int PER = 32 * CW / (64 * MS), RSTEP = 64 * MS / CW;
-  __shared__ __attribute__((aligned(16))) unsigned short xb[2][6][CW][KP];
+  constexpr int RP = PER > 1 ? 2 : 1;  // consecutive rows a thread stages together
+  __shared__ __attribute__((aligned(16))) unsigned short xb[2][6][NB][64][8];
   if (a.tcount && (int)blockIdx.x >= *a.tcount) return;
   const TileDesc t0 = a.tiles[blockIdx.x];
   if (t0.f < 0) return;
@@ -322,7 +336,7 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_bf16m(PassArgs a) {
   const bool act = t.rb < ((L + 15) >> 4);
   const v8bf* zb = reinterpret_cast<const v8bf*>(a.zero);
   const v8bf* P = reinterpret_cast<const v8bf*>(reinterpret_cast<const char*>(a.P) + t.poff) +
-                  (int64_t)(act ? t.rb : 0) * nkc * 6 * 64 + lane;
+                  (int64_t)(act ? t.rb : 0) * nkc * 6 * 64;
   int wc[NB];
   bool wok[NB];
   tile_cols<NB>(a, t, li, wc, wok);
@@ -335,46 +349,54 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_bf16m(PassArgs a) {
     sok = sl < nc;
     sw = a.cols ? (sok ? a.cols[(int64_t)t.f * a.W + sl] : 0) : sl;
   }
-  const double2* zx = reinterpret_cast<const double2*>(a.zero);
   v4f rr[NB], ii[NB], ri[NB], ir[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) rr[nb] = ii[nb] = ri[nb] = ir[nb] = (v4f){0.f, 0.f, 0.f, 0.f};
   double2 sv[PER];
-  // State operands of chunk kc (rows past the fibre read the zero buffer).  The offset is
-  // computed unconditionally and pinned by an empty asm operand, so the pointer select stays a
-  // select: a load under a branch makes the compiler wait for every outstanding load at the
-  // join, including the next chunk's prefetch.  (Pinning the pointer itself would lose its
-  // address space and turn the loads into flat loads, which LDS waits also wait for.)
-  auto load_state = [&](int kc) {
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int k = 32 * kc + rr0 + j * RSTEP;
-      const bool ok = sok && k < L;
-      int64_t off = xrow<GATHER>(a, r0 + (ok ? k : 0)) * a.W + sw;
-      asm volatile("" : "+v"(off));
-      sv[j] = *(ok ? a.X + off : zx);
-    }
-  };
-  // fp32(x) split exactly into three bf16 terms, six planes [term re/im][column][k]
+  // State operands of chunk kc (rows past the fibre read zeros): rows RP (rr0 + RSTEP j) + q of the
+  // chunk, q < RP
+  const int64_t zoff = byte_distance(a.X, a.zero), row_bytes = (int64_t)a.W * 16;
+  auto row_of = [&](int e) { return RP * (rr0 + (e / RP) * RSTEP) + e % RP; };
+  // fp32(x) split exactly into three bf16 terms, six planes [term re/im]
+  const int sb = c >> 4, sc = c & 15;
   auto store_state = [&](int buf) {
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      unsigned short q0, q1, q2, q3, q4, q5;
-      split3x((float)sv[j].x, q0, q1, q2);
-      split3x((float)sv[j].y, q3, q4, q5);
-      const int k = rr0 + j * RSTEP;
-      xb[buf][0][c][k] = q0;
-      xb[buf][1][c][k] = q1;
-      xb[buf][2][c][k] = q2;
-      xb[buf][3][c][k] = q3;
-      xb[buf][4][c][k] = q4;
-      xb[buf][5][c][k] = q5;
+    for (int e = 0; e < PER; e += RP) {
+      unsigned short q[RP][6];
+#pragma unroll
+      for (int r = 0; r < RP; ++r) {
+        split3x((float)sv[e + r].x, q[r][0], q[r][1], q[r][2]);
+        split3x((float)sv[e + r].y, q[r][3], q[r][4], q[r][5]);
+      }
+      const int k = row_of(e);
+#pragma unroll
+      for (int pl = 0; pl < 6; ++pl) {
+        unsigned short* to = &xb[buf][pl][sb][sc + 16 * (k >> 3)][k & 7];
+        if (RP == 2)
+          *reinterpret_cast<unsigned*>(to) = (unsigned)q[0][pl] | ((unsigned)q[RP - 1][pl] << 16);
+        else
+          *to = q[0][pl];
+      }
     }
   };
   // the tile's band of chunks [klo, khi), and this wave's own [wlo, whi) inside it (its row
   // block's band; the staged chunks cover the union)
   int klo, khi;
   tile_band(t0, 32 * nkc, 32, klo, khi);
+  // byte offset of this thread's first element of the chunk that load_state reads next (chunks in
+  // order from klo)
+  int64_t off0 = (int64_t)(r0 + 32 * klo + RP * rr0) * row_bytes + (int64_t)sw * 16;
+  auto load_state = [&](int kc) {
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int k = 32 * kc + row_of(e);
+      const bool ok = sok && k < L;
+      const int64_t off = GATHER ? xrow<GATHER>(a, r0 + (ok ? k : 0)) * row_bytes + (int64_t)sw * 16
+                                 : off0 + (int64_t)(RP * (e / RP) * RSTEP + e % RP) * row_bytes;
+      sv[e] = load_or_zero(a.X, ok, off, zoff);
+    }
+    off0 += 32 * row_bytes;
+  };
   int wlo = klo, whi = khi;
   if (a.rb_band && t0.bb >= 0 && act) {
     const int2 wb = reinterpret_cast<const int2*>(a.rb_band)[t0.bb + t.rb];
@@ -382,58 +404,59 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_bf16m(PassArgs a) {
     whi = (min(wb.y, 32 * nkc) + 31) / 32;
   }
   auto mine = [&](int kc) { return act && kc >= wlo && kc < whi; };
-  // this wave's propagator planes of chunk kc (E re/im terms 0..2), zeros outside its band
-  auto load_e = [&](v8bf (&E)[6], int kc) {
+  // propagator planes of chunk kc, real (part 0) or imaginary (part 1) terms 0..2, zeros outside
+  // the wave's band: a uniform address and the lane
+  v8bf E[2][3];
+  auto load_e = [&](int part, int kc) {
     const bool in = mine(kc);
 #pragma unroll
-    for (int pl = 0; pl < 6; ++pl) {
-      int64_t off = ((int64_t)kc * 6 + pl) * 64;
-      asm volatile("" : "+v"(off));
-      E[pl] = *(in ? P + off : zb);
+    for (int q = 0; q < 3; ++q) {
+      const v8bf* p = in ? P + ((int64_t)kc * 6 + 2 * q + part) * 64 : zb;
+      E[part][q] = p[(unsigned)lane];
     }
   };
-  auto mma = [&](const v8bf (&E)[6], int buf) {
+  // products of one part's planes with both parts of the staged chunk: part 0 into rr and ri, part
+  // 1 into ir and ii
+  auto mma = [&](int part, int buf) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       // one column block's operands at a time (keeps the next block's LDS reads from being
       // hoisted, which would hold twice the registers)
       if (nb > 0) __builtin_amdgcn_sched_barrier(0);
-      const int col = nb * 16 + li;
-      const v8bf Xr0 = *reinterpret_cast<const v8bf*>(&xb[buf][0][col][8 * lk]);
-      const v8bf Xr1 = *reinterpret_cast<const v8bf*>(&xb[buf][1][col][8 * lk]);
-      const v8bf Xr2 = *reinterpret_cast<const v8bf*>(&xb[buf][2][col][8 * lk]);
-      const v8bf Xi0 = *reinterpret_cast<const v8bf*>(&xb[buf][3][col][8 * lk]);
-      const v8bf Xi1 = *reinterpret_cast<const v8bf*>(&xb[buf][4][col][8 * lk]);
-      const v8bf Xi2 = *reinterpret_cast<const v8bf*>(&xb[buf][5][col][8 * lk]);
-      rr[nb] = mma3(rr[nb], E[0], E[2], E[4], Xr0, Xr1, Xr2);
-      ii[nb] = mma3(ii[nb], E[1], E[3], E[5], Xi0, Xi1, Xi2);
-      ri[nb] = mma3(ri[nb], E[0], E[2], E[4], Xi0, Xi1, Xi2);
-      ir[nb] = mma3(ir[nb], E[1], E[3], E[5], Xr0, Xr1, Xr2);
+      v8bf X[6];
+#pragma unroll
+      for (int q = 0; q < 6; ++q) X[q] = *reinterpret_cast<const v8bf*>(&xb[buf][q][nb][lane][0]);
+      if (part == 0) {
+        rr[nb] = mma3(rr[nb], E[0][0], E[0][1], E[0][2], X[0], X[1], X[2]);
+        ri[nb] = mma3(ri[nb], E[0][0], E[0][1], E[0][2], X[3], X[4], X[5]);
+      } else {
+        ii[nb] = mma3(ii[nb], E[1][0], E[1][1], E[1][2], X[3], X[4], X[5]);
+        ir[nb] = mma3(ir[nb], E[1][0], E[1][1], E[1][2], X[0], X[1], X[2]);
+      }
     }
   };
-  // Ping-pong operand buffers over pairs of chunks: chunk kc multiplies EA (or EB) while the
-  // next chunk's state values and planes load into sv and EB (or EA); no register copies.
-  v8bf EA[6], EB[6];
+  // Chunk kc: its real planes' products, then the next chunk's real planes into the same
+  // registers, then the imaginary ones alike: each set of planes is loaded half a chunk of
+  // products ahead of its use, without a second set of registers.
   load_state(klo);
-  load_e(EA, klo);
+  load_e(0, klo);
+  load_e(1, klo);
   store_state(0);
   __syncthreads();
-  for (int kc = klo; kc < khi; kc += 2) {
+  for (int kc = klo; kc < khi; ++kc) {
+    const int buf = (kc - klo) & 1;
+    const bool in = mine(kc);
     load_state(kc + 1);
-    load_e(EB, kc + 1);
     __builtin_amdgcn_sched_barrier(0);
-    if (mine(kc)) mma(EA, 0);
+    if (in) mma(0, buf);
     __builtin_amdgcn_sched_barrier(0);
+    load_e(0, kc + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (in) mma(1, buf);
+    __builtin_amdgcn_sched_barrier(0);
+    load_e(1, kc + 1);
     if (kc + 1 >= khi) break;
-    store_state(1);
-    __syncthreads();
-    load_state(kc + 2);
-    load_e(EA, kc + 2);
-    __builtin_amdgcn_sched_barrier(0);
-    if (mine(kc + 1)) mma(EB, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    if (kc + 2 >= khi) break;
-    store_state(0);
+    store_state(buf ^ 1);
     __syncthreads();
   }
   if (!act) return;
