@@ -1524,9 +1524,12 @@ extern "C" lsx_status lsx_plan_destroy(lsx_plan* pl) {
 struct lsx_state {
   lsx_plan* plan = nullptr;
   int W = 0;
-  double2* buf[2] = {nullptr, nullptr};
+  // the state (canonical order between calls), the work array, and for wrapped states a second
+  // work array (null: no memory for it), with which a call's last pass can write buf[0] whatever
+  // their number: the passes between alternate between the two work arrays
+  double2* buf[3] = {nullptr, nullptr, nullptr};
   bool owns0 = false;
-  DBuf<double2> own0, work;
+  DBuf<double2> own0, work, work2;
   DBuf<TileDesc> tiles[kMaxLayers];
   int ntiles[kMaxLayers] = {0, 0, 0};
   int nb[kMaxLayers] = {1, 1, 1}, ks[kMaxLayers] = {4, 4, 4};  // tile shape per layer (16*nb columns, ks waves split k)
@@ -2027,6 +2030,10 @@ extern "C" lsx_status lsx_state_create(lsx_plan* pl, int32_t W, void* dev_ptr, l
   }
   if ((e = st->work.alloc(total)) != LSX_OK) return cleanup(e);
   st->buf[1] = st->work.p;
+  // a state whose arrays cannot swap roles would copy its result home after an odd number of
+  // passes (0.33 of the twisted bilayer's 9.6 ms for two FP64 steps, 0.35 of the trilayer's 3.1 ms for
+  // one FP32 step at W = 128)
+  if (dev_ptr && st->work2.alloc(total) == LSX_OK) st->buf[2] = st->work2.p;
   if ((e = choose_tiles(pl, st)) != LSX_OK) return cleanup(e);
   st->nred = (int)std::max<int64_t>(1, std::min<int64_t>(1024, (N + 255) / 256));
   // observables: mass, energy and the fibre masses of every layer in one result block
@@ -2157,7 +2164,7 @@ extern "C" lsx_status lsx_state_destroy(lsx_state* st) {
 
 // ================================================================ step composer
 // Between API calls the state lives in buf[0] in canonical order.  A fibre pass reads
-// buf[cur] and writes buf[1-cur].  Array layouts: layout j = layer-j fibre order, layout nl =
+// buf[cur] and writes buf[target()].  Array layouts: layout j = layer-j fibre order, layout nl =
 // canonical (the last layer's fibres are contiguous runs).  A pass writes the layout the next
 // pass reads fibre-contiguously, so only the first pass of a call gathers through an index
 // table; the last pass writes canonical order.  The kinetic phase that follows a pass is
@@ -2171,6 +2178,15 @@ struct Runner {
   int lay = 0;  // layout of buf[cur]; 0 = canonical
 
   const int32_t* table(int layer, int layout) const { return layout_map(pl, layer, layout); }
+
+  // Array the next pass writes: the other one of two; with a second work array the call's last
+  // pass writes the state itself (unless it reads it) and the others alternate between the work
+  // arrays.
+  int target(bool last) const {
+    if (!st->buf[2]) return 1 - cur;
+    if (cur == 0) return 1;
+    return last ? 0 : 3 - cur;
+  }
 
   // F_layer(t) with t = tau (half 0) or tau/2; `next` is the layer of the following
   // pass (0: none, write canonical order); phase_half >= 0 fuses Phase(kappa t') after it.
@@ -2189,8 +2205,9 @@ struct Runner {
     a.ph = (phase_half >= 0 && pl->kappa != 0.0) ? pl->phase[phase_half].p : nullptr;
     a.P = ps.data.p;
     a.diag = pl->diag.p ? pl->diag.p + (size_t)((layer - 1) * 3 + half) * pl->sys->N : nullptr;
+    const int to = target(next == 0);
     a.X = st->buf[cur];
-    a.Y = st->buf[1 - cur];
+    a.Y = st->buf[to];
     a.zero = pl->zero.p;
     a.rb_band = ld.d_band.p;
     a.orbit = ld.d_orbit.p;
@@ -2200,7 +2217,7 @@ struct Runner {
     a.u = st->u[layer - 1];
     LSX_HIP_TRY(launch_pass(s, pl->fmt, st->W, st->ntiles[layer - 1], st->nb[layer - 1],
                             pass_waves(pl, layer, st->W, st->nb[layer - 1], st->ks[layer - 1]), a));
-    cur ^= 1;
+    cur = to;
     lay = outlay;
     return LSX_OK;
   }
@@ -2216,7 +2233,7 @@ struct Runner {
         // both arrays belong to the library: swap roles instead of copying
         std::swap(st->buf[0], st->buf[1]);
       } else {
-        LSX_HIP_TRY(hipMemcpyAsync(st->buf[0], st->buf[1], (size_t)pl->sys->N * st->W * sizeof(double2),
+        LSX_HIP_TRY(hipMemcpyAsync(st->buf[0], st->buf[cur], (size_t)pl->sys->N * st->W * sizeof(double2),
                                    hipMemcpyDeviceToDevice, s));
       }
       cur = 0;
@@ -2556,6 +2573,8 @@ struct lsx_batch {
   // through an index table (then the launch uses the gathering kernel for every system)
   std::map<PatternKey, std::pair<std::unique_ptr<DBuf<PassArgs>>, bool>> args;
   std::vector<std::pair<double2*, double2*>> bufs;  // buffers the argument arrays refer to
+  DBuf<CopyItem> home;                               // per system: work array to state array
+  int64_t home_max = 0;                              // elements of the largest
   DBuf<int32_t> marker;                              // non-null in_pos marker for gathering passes
   DBuf<int32_t> queue;                               // persistent launches: 9 counters, zero between launches
   int u[kMaxLayers] = {0, 0, 0};                     // K-split FP64/FP32: k-step groups in flight (0: 2)
@@ -2575,6 +2594,18 @@ struct lsx_batch {
 // index table of `layer`'s fibre positions inside an array of layout `layout` (two layers)
 static const int32_t* layout_table(const lsx_plan* pl, int layer, int layout) {
   return layout_map(pl, layer, layout);
+}
+
+// the systems' copies from work array to state array, for the arrays they have now
+static lsx_status batch_home(lsx_batch* b) {
+  std::vector<CopyItem> v;
+  b->home_max = 0;
+  for (const lsx_state* st : b->st) {
+    const int64_t n = st->plan->sys->N * st->W;
+    v.push_back({st->buf[1], st->buf[0], n});
+    b->home_max = std::max(b->home_max, n);
+  }
+  return b->home.upload(v, nullptr);
 }
 
 // replays still running finish first
@@ -2861,6 +2892,7 @@ extern "C" lsx_status lsx_batch_create(lsx_plan* const* plans, lsx_state* const*
         if (prepare_persistent(b->fmt, b->w1 ? 1 : 2, b->nb[layer - 1], b->ks[layer - 1], a0) != hipSuccess)
           return cleanup(fail(LSX_E_HIP, "persistent launch setup failed"));
       }
+  if ((e = batch_home(b)) != LSX_OK) return cleanup(e);
   if (hipDeviceSynchronize() != hipSuccess) return cleanup(fail(LSX_E_HIP, "batch setup failed"));
   for (lsx_state* st : b->st) st->nbatches++;
   for (lsx_state* st : b->st) b->bufs.emplace_back(st->buf[0], st->buf[1]);
@@ -2879,6 +2911,7 @@ extern "C" lsx_status lsx_batch_step(lsx_batch* b, int64_t nsteps, void* stream)
       b->args.clear();
       batch_drop_graph(b);
       for (size_t j = 0; j < b->st.size(); ++j) b->bufs[j] = {b->st[j]->buf[0], b->st[j]->buf[1]};
+      LSX_TRY(batch_home(b));
       break;
     }
   std::vector<PassSpec> head, body, tail;
@@ -2947,11 +2980,8 @@ extern "C" lsx_status lsx_batch_step(lsx_batch* b, int64_t nsteps, void* stream)
   for (int64_t r = 0; r < extra; ++r)
     for (const PassSpec& p : body) LSX_TRY(batch_pass(b, s, p, cur, lay));
   for (const PassSpec& p : tail) LSX_TRY(batch_pass(b, s, p, cur, lay));
-  if (cur != 0) {
-    for (lsx_state* st : b->st)
-      LSX_HIP_TRY(hipMemcpyAsync(st->buf[0], st->buf[1], (size_t)st->plan->sys->N * st->W * sizeof(double2),
-                                 hipMemcpyDeviceToDevice, s));
-  }
+  // results home after an odd number of passes: every system in one launch
+  if (cur != 0) LSX_HIP_TRY(launch_copy_home(s, (int)b->st.size(), b->home.p, b->home_max));
   return LSX_OK;
 }
 
@@ -3340,14 +3370,16 @@ lsx_status phase_canon(lsx_plan* pl, lsx_state* st, int half, hipStream_t s) {
   return LSX_OK;
 }
 
-// Alg. 1 / Alg. 4 step from the runner's current array into the other one
-lsx_status si_once(Runner& r, const double* wt1, const int32_t* fid1, const double* wt2, const int32_t* fid2) {
+// Alg. 1 / Alg. 4 step from the runner's current array into its next one (last: of the call)
+lsx_status si_once(Runner& r, bool last, const double* wt1, const int32_t* fid1, const double* wt2,
+                   const int32_t* fid2) {
+  const int to = r.target(last);
   lsx_plan* pl = r.pl;
   const lsx_system* sys = pl->sys;
   LSX_HIP_TRY(launch_si_step(r.s, pl->sweep, r.st->W, pl->tau, pl->K2.p, sys->pot[0].nv, pl->L[0].nbr.p, pl->L[0].v.p,
                              wt1, fid1, sys->pot[1].nv, pl->L[1].nbr.p, pl->L[1].v.p, wt2, fid2, r.st->buf[r.cur],
-                             r.st->buf[1 - r.cur], pl->zero.p));
-  r.cur ^= 1;
+                             r.st->buf[to], pl->zero.p));
+  r.cur = to;
   return LSX_OK;
 }
 }  // namespace
@@ -3360,7 +3392,7 @@ extern "C" lsx_status lsx_si_step(lsx_plan* pl, lsx_state* st, int64_t nsteps, v
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if (pl->sys->N == 0) return LSX_OK;
   return run_passes(pl, st, s, [&](Runner& r) -> lsx_status {
-    for (int64_t k = 0; k < nsteps; ++k) LSX_TRY(si_once(r, nullptr, nullptr, nullptr, nullptr));
+    for (int64_t k = 0; k < nsteps; ++k) LSX_TRY(si_once(r, k + 1 == nsteps, nullptr, nullptr, nullptr, nullptr));
     return LSX_OK;
   });
 }
@@ -3379,7 +3411,7 @@ extern "C" lsx_status lsx_rb_step(lsx_sampler* sm, const double* u, int64_t nste
     for (int64_t k = 0; k < nsteps; ++k) {
       for (int j = 0; j < 2; ++j)
         LSX_HIP_TRY(launch_subset_weights(s, sm->nf[j], W, sm->p[j], pmax, u + (2 * k + j) * per, sm->wt[j].p));
-      LSX_TRY(si_once(r, sm->wt[0].p, sm->fid[0].p, sm->wt[1].p, sm->fid[1].p));
+      LSX_TRY(si_once(r, k + 1 == nsteps, sm->wt[0].p, sm->fid[0].p, sm->wt[1].p, sm->fid[1].p));
     }
     return LSX_OK;
   });

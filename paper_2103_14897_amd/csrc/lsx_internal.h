@@ -220,6 +220,13 @@ struct ReduceArgs {
   double* penergy = nullptr;
 };
 hipError_t launch_reduce(hipStream_t s, const ReduceArgs& a, int nblocks, double* mass, double* energy);
+// n copies of whole arrays in one launch (max_elems: the longest)
+struct CopyItem {
+  const double2* from;
+  double2* to;
+  int64_t elems;
+};
+hipError_t launch_copy_home(hipStream_t s, int n, const CopyItem* items, int64_t max_elems);
 hipError_t launch_fibre_mass(hipStream_t s, int nf, const int32_t* ptr, const int32_t* rows, int W,
                              const double2* c, double* out);
 // Device address of this GPU's static scratch array (kStaticScratchDoubles doubles), looked up
