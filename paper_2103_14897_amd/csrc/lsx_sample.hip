@@ -386,6 +386,11 @@ typedef float mlp_v4f __attribute__((ext_vector_type(4)));
 constexpr int MLP_CH = 16;    // rows per wave chunk
 constexpr int MLP_LDT = 68;   // LDS row stride of a chunk's 64-wide tiles (floats)
 constexpr int MLP_WTILE = 2 * MLP_CH * MLP_LDT + MLP_CH * MLP_NIN_MAX;  // per-wave LDS (H1, D, X)
+// LDS row stride of the backward pass's copy of W2, read both along its rows (lane 16 lk + li at row
+// lk, column li) and across them (row li, column lk): 84 = 64 + 20 floats put the 64 lanes of the
+// second pattern on 64 different banks and the first on at most two per bank, where a stride of 64
+// gave 16 and 4 lanes per bank (backward pass over 1.14e6 rows: 680 to 545 us)
+constexpr int MLP_LDW = 84;
 
 // W2 in the B layout: w2[kk][ct] = W2[4 kk + lk][16 ct + li]
 __device__ __forceinline__ void mlp_w2_frag(const float* sp, const MlpOff& o, int li, int lk, float (&w2)[16][4]) {
@@ -401,7 +406,8 @@ __device__ __forceinline__ void mlp_w2_frag(const float* sp, const MlpOff& o, in
 // from the staged parameters in LDS.
 template <bool REG>
 __device__ __forceinline__ void mlp_hidden(const float* sp, const MlpOff& o, int nin, const float (&x)[MLP_NIN_MAX],
-                                           int li, int lk, const float (*w2)[4], mlp_v4f (&acc)[4], float* H1) {
+                                           int li, int lk, const float (*w2)[4], const float* W2, mlp_v4f (&acc)[4],
+                                           float* H1) {
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) acc[ct] = (mlp_v4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -415,7 +421,7 @@ __device__ __forceinline__ void mlp_hidden(const float* sp, const MlpOff& o, int
     if (H1) H1[li * MLP_LDT + j] = h;
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
-      const float b = REG ? w2[kk][ct] : sp[o.W2 + (4 * kk + lk) * MLP_H + 16 * ct + li];
+      const float b = REG ? w2[kk][ct] : W2[(4 * kk + lk) * MLP_LDW + 16 * ct + li];
       acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(h, b, acc[ct], 0, 0, 0);
     }
   }
@@ -440,7 +446,7 @@ __global__ LSX_MFMA_BOUNDS(256, true) void k_mlp_fwd(const float* theta, int nin
     float x[MLP_NIN_MAX];
     mlp_load_row(X, M, nin, c * MLP_CH + li, x);
     mlp_v4f acc[4];
-    mlp_hidden<true>(sp, o, nin, x, li, lk, w2, acc, nullptr);
+    mlp_hidden<true>(sp, o, nin, x, li, lk, w2, nullptr, acc, nullptr);
     float zr[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -470,10 +476,12 @@ __global__ LSX_MFMA_BOUNDS(256, true) void k_mlp_bwd(const float* theta, int nin
   extern __shared__ float sp[];
   const MlpOff o(nin);
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4, wave = threadIdx.x >> 6;
-  float* H1 = sp + ((o.n + 3) & ~3) + wave * MLP_WTILE;
+  float* W2 = sp + ((o.n + 3) & ~3);
+  float* H1 = W2 + MLP_H * MLP_LDW + wave * MLP_WTILE;
   float* D = H1 + MLP_CH * MLP_LDT;
   float* XS = D + MLP_CH * MLP_LDT;
   mlp_stage(theta, o.n, sp);
+  for (int e = threadIdx.x; e < MLP_H * MLP_H; e += 256) W2[(e >> 6) * MLP_LDW + (e & 63)] = theta[o.W2 + e];
   __syncthreads();
   const float gs = gscale ? (float)*gscale : 1.f;
   float b2[4], w3[4];
@@ -499,7 +507,7 @@ __global__ LSX_MFMA_BOUNDS(256, true) void k_mlp_bwd(const float* theta, int nin
 #pragma unroll
       for (int i = 0; i < MLP_NIN_MAX; ++i) XS[li * MLP_NIN_MAX + i] = x[i];
     mlp_v4f acc[4];
-    mlp_hidden<false>(sp, o, nin, x, li, lk, nullptr, acc, H1);
+    mlp_hidden<false>(sp, o, nin, x, li, lk, nullptr, W2, acc, H1);
     float g[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -546,8 +554,7 @@ __global__ LSX_MFMA_BOUNDS(256, true) void k_mlp_bwd(const float* theta, int nin
       const float a = D[li * MLP_LDT + 4 * kk + lk];
 #pragma unroll
       for (int jt = 0; jt < 4; ++jt)
-        e[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, sp[o.W2 + (16 * jt + li) * MLP_H + 4 * kk + lk], e[jt], 0,
-                                                     0, 0);
+        e[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, W2[(16 * jt + li) * MLP_LDW + 4 * kk + lk], e[jt], 0, 0, 0);
     }
     // d1 = e (1 - h1^2), written over d2 (every lane has read its d2 operands above)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -614,13 +621,23 @@ __global__ LSX_MFMA_BOUNDS(256, true) void k_mlp_bwd(const float* theta, int nin
   for (int k = threadIdx.x; k < o.n; k += blockDim.x) out[k] = sp[k];
 }
 
-// grad[e] = sum over workgroups of partial[b][e] (FP64, fixed order)
-__global__ __launch_bounds__(256) void k_mlp_reduce(int nparts, int n, const float* partial, float* grad) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
+// grad[e] = sum over workgroups of partial[b][e] (FP64, fixed order): 64 entries per workgroup, 16
+// threads per entry each taking every 16th partial (one thread per entry walked up to 512 of them
+// one after the other: 124 us for 4609 entries and 512 partials, 11 us now)
+__global__ __launch_bounds__(1024) void k_mlp_reduce(int nparts, int n, const float* partial, float* grad) {
+  __shared__ double red[16][64];
+  const int te = threadIdx.x & 63, tp = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + te;
   double s = 0.0;
-  for (int b = 0; b < nparts; ++b) s += partial[(int64_t)b * n + e];
-  grad[e] = (float)s;
+  if (e < n)
+    for (int b = tp; b < nparts; b += 16) s += partial[(int64_t)b * n + e];
+  red[tp][te] = s;
+  __syncthreads();
+  if (tp == 0 && e < n) {
+    double t = 0.0;
+    for (int k = 0; k < 16; ++k) t += red[k][te];
+    grad[e] = (float)t;
+  }
 }
 
 // Variance objective per group g (rows gptr[g]..gptr[g+1]), one workgroup per group:
@@ -801,7 +818,7 @@ hipError_t launch_features(hipStream_t s, int nf, int W, int d, const double* sf
 
 static size_t mlp_lds_fwd(int nin) { return (size_t)((MlpOff(nin).n + 3) & ~3) * sizeof(float); }
 static size_t mlp_lds_bwd(int nin) {
-  return (size_t)(((MlpOff(nin).n + 3) & ~3) + 4 * MLP_WTILE) * sizeof(float);
+  return (size_t)(((MlpOff(nin).n + 3) & ~3) + MLP_H * MLP_LDW + 4 * MLP_WTILE) * sizeof(float);
 }
 
 // workgroups of the backward pass (4 waves of 16-row chunks each): one partial gradient each
@@ -825,7 +842,7 @@ hipError_t launch_mlp_bwd(hipStream_t s, const float* theta, int nin, const floa
   hipLaunchKernelGGL(k_mlp_bwd, dim3(nparts), dim3(256), mlp_lds_bwd(nin), s, theta, nin, X, M, dz, gscale, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((n + 255) / 256), dim3(256), 0, s, nparts, n, partial, grad);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((n + 63) / 64), dim3(1024), 0, s, nparts, n, partial, grad);
   return hipGetLastError();
 }
 
