@@ -636,6 +636,9 @@ struct LayerDev {
   std::vector<std::vector<int>> groups;
   DBuf<int32_t> d_orbit;
   int orbit_max = 0;
+  DBuf<ResidentRow> resident;  // row table of the resident steps (small systems only)
+  int64_t band_bytes = 0;      // propagator bytes inside the bands of one pass
+  int band_steps = 0;          // k-steps of the widest band
 };
 
 // Band of row blocks [rb0, rb0 + n) of fibre f (those inside the fibre) as fibre positions
@@ -989,6 +992,38 @@ static lsx_status block_jacobi(hipStream_t s, const std::vector<int32_t>& sel, c
   return LSX_OK;
 }
 
+// Resident steps hold two copies of a column in LDS: 2048 rows are 64 KB.
+static constexpr int64_t kResidentMaxRows = 2048;
+// Row table of the resident steps and the propagator bytes a pass reads per column.
+static lsx_status resident_rows(lsx_plan* pl, int layer, hipStream_t s) {
+  LayerDev& ld = pl->L[layer - 1];
+  const int64_t N = pl->sys->N;
+  const int esz = pl->fmt == PF_F64 ? 16 : 8, unit = band_chunk(pl->fmt);
+  ld.band_bytes = 0;
+  ld.band_steps = 0;
+  std::vector<ResidentRow> rows;
+  if (N <= kResidentMaxRows) rows.resize((size_t)N);
+  for (int f = 0; f < ld.nf; ++f) {
+    const int r0 = ld.h_ptr[f], L = ld.h_ptr[f + 1] - r0, Lp = round_up(L, prop_pad(pl->fmt));
+    for (int rb = 0; rb < (L + 15) / 16; ++rb) {
+      int32_t k0, k1;
+      fibre_band(ld, f, rb, 1, k0, k1);
+      const int c0 = k0 / unit, n = (std::min(k1, Lp) + unit - 1) / unit - c0;
+      ld.band_steps = std::max(ld.band_steps, n);
+      ld.band_bytes += (int64_t)std::min(16, L - 16 * rb) * n * unit * (pl->fmt == PF_BF16X3 ? 12 : esz);
+      if (rows.empty()) continue;
+      // element (of 16 lanes x 8 bf16 for BF16x3) of lane 0 in the band's first chunk
+      const int64_t chunk = (int64_t)rb * (Lp / unit) + c0;
+      const int64_t first = pl->fmt == PF_BF16X3 ? ld.h_poff[f] / 16 + chunk * 6 * 64 : ld.h_poff[f] / esz + chunk * 64;
+      for (int a = 16 * rb; a < std::min(L, 16 * rb + 16); ++a)
+        rows[(size_t)r0 + a] = {first + a % 16, r0 + c0 * unit, r0 + L, n, ld.h_d0[f] + a,
+                                 ld.h_rows[(size_t)r0 + a], 0};
+    }
+  }
+  if (rows.empty()) return LSX_OK;
+  return ld.resident.upload(rows, s);
+}
+
 static lsx_status precompute_layer(lsx_plan* pl, int layer, hipStream_t s) {
   lsx_system* sys = pl->sys;
   LayerDev& ld = pl->L[layer - 1];
@@ -1200,6 +1235,7 @@ static lsx_status precompute_layer(lsx_plan* pl, int layer, hipStream_t s) {
     }
     LSX_TRY(ld.d_band.upload(hband, s));
   }
+  LSX_TRY(resident_rows(pl, layer, s));
   LSX_HIP_TRY(hipStreamSynchronize(s));
   return LSX_OK;
 }
@@ -2352,6 +2388,68 @@ void step_sequence(int scheme, int nl, int64_t nsteps, std::vector<PassSpec>& he
 }
 }  // namespace
 
+// Whether a call's passes run as one resident launch (lsx_resident.hip): a single state in any
+// precision or FP64 columns (whose arithmetic the resident passes share), a column that fits LDS,
+// and either a body whose two passes fit the registers (`pair`), or few enough propagator bytes per
+// pass that one workgroup reads them once per column sooner than a launch over the whole chip
+// ends.  Microseconds per Strang step, launches / resident, FP64 chains of W = 1: N = 53 (pair) 5.6 /
+// 1.05, N = 155 (pair) 5.4 / 1.5, three layers N = 127 (11 KB) 9.7 / 4.8, without pairs 36 KB 5.5 / 3.5,
+// 50 KB 5.8 / 4.5, 122 KB 5.9 / 8.7; W = 256 as W = 1 (one workgroup per CU).
+static constexpr int64_t kResidentBytes = 49152;
+static constexpr int kResidentPairRows = 256, kResidentPairMaxW = 1024;
+static bool resident_pair(const lsx_plan* pl, size_t nbody) {
+  bool pair = pl->fmt != PF_BF16X3 && nbody == 2 && pl->sys->N <= kResidentPairRows;
+  for (int j = 0; j < pl->sys->nl; ++j) pair = pair && pl->L[j].band_steps <= kResidentU;
+  return pair;
+}
+static bool use_resident(const lsx_plan* pl, const lsx_state* st, size_t npass, size_t nbody) {
+  if (pl->sys->N > kResidentMaxRows || (st->W > 1 && pl->fmt != PF_F64) || npass > (size_t)kResidentPasses) return false;
+  if (resident_pair(pl, nbody)) return st->W <= kResidentPairMaxW;
+  int64_t most = 0;
+  for (int j = 0; j < pl->sys->nl; ++j) most = std::max(most, pl->L[j].band_bytes);
+  return most * ((st->W + 255) / 256) <= kResidentBytes;
+}
+
+// The sequence head, body x reps, tail as resident launches of at most kResidentSpan passes each (a
+// bounded run time), in place on the state array.
+static constexpr int64_t kResidentSpan = 16384;
+static lsx_status resident_steps(lsx_plan* pl, lsx_state* st, hipStream_t s, const std::vector<PassSpec>& head,
+                                 const std::vector<PassSpec>& body, const std::vector<PassSpec>& tail, int64_t reps) {
+  ResidentArgs a;
+  int n = 0;
+  for (const std::vector<PassSpec>* part : {&head, &body, &tail})
+    for (const PassSpec& p : *part) {
+      const LayerDev& ld = pl->L[p.layer - 1];
+      const PropSet& ps = ld.prop[p.half];
+      if (!ps.present) return fail(LSX_E_INVALID, "plan holds no propagator for this layer/slot");
+      if (p.phase_half >= 0 && pl->kappa != 0.0 && !pl->phase[p.phase_half].p)
+        return fail(LSX_E_INVALID, "plan holds no phase table for this slot");
+      ResidentPass& d = a.pass[n++];
+      d.rows = ld.resident.p;
+      d.out_pos = layout_map(pl, p.layer, p.next);
+      d.ph = (p.phase_half >= 0 && pl->kappa != 0.0) ? pl->phase[p.phase_half].p : nullptr;
+      d.P = ps.data.p;
+      d.diag = pl->diag.p ? pl->diag.p + (size_t)((p.layer - 1) * 3 + p.half) * pl->sys->N : nullptr;
+    }
+  a.nhead = (int)head.size();
+  a.nbody = (int)body.size();
+  a.ntail = (int)tail.size();
+  a.reps = body.empty() ? 0 : reps;
+  a.N = (int)pl->sys->N;
+  a.W = st->W;
+  a.X = a.Y = st->buf[0];
+  const int64_t total = a.nhead + a.nbody * a.reps + a.ntail;
+  const std::vector<PassSpec>& f = !head.empty() ? head : (a.reps > 0 ? body : tail);
+  a.in_pos = layout_map(pl, f[0].layer, 0);
+  const bool pair = resident_pair(pl, body.size());
+  for (a.begin = 0; a.begin < total; a.begin = a.end) {
+    a.end = std::min(total, a.begin + kResidentSpan);
+    LSX_HIP_TRY(launch_resident(s, pl->fmt, a, pair));
+    a.in_pos = nullptr;  // later launches find the state in the order the last one left it in
+  }
+  return LSX_OK;
+}
+
 extern "C" lsx_status lsx_step(lsx_plan* pl, lsx_state* st, int64_t nsteps, void* stream) {
   LSX_TRY(check_pair(pl, st));
   if (nsteps < 0) return fail(LSX_E_INVALID, "nsteps must be >= 0");
@@ -2360,6 +2458,8 @@ extern "C" lsx_status lsx_step(lsx_plan* pl, lsx_state* st, int64_t nsteps, void
   int64_t reps = 0;
   step_sequence(pl->scheme, pl->sys->nl, nsteps, head, body, tail, reps);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if (use_resident(pl, st, head.size() + body.size() + tail.size(), body.size()))
+    return resident_steps(pl, st, s, head, body, tail, reps);
   // body repetitions per captured graph (the ladder): about graph_passes() passes for the bulk
   // of the call, then halved sizes down to about graph_min_passes() passes for its remainder,
   // each an even number of passes so that a replay ends in the arrays and layout it starts from

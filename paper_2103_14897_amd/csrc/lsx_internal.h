@@ -219,6 +219,38 @@ struct ReduceArgs {
   double* pmass = nullptr;
   double* penergy = nullptr;
 };
+// Resident steps (lsx_resident.hip).  Row p of a layer's order: its propagator's first stored
+// element of the row's band (lane 0 of the four that share the row), the state position of the
+// band's first column, one past the fibre's last, the number of k-steps (chunks for BF16x3), the
+// position of its diagonal entry and its canonical index.
+struct ResidentRow {
+  int64_t base;
+  int32_t x0, lim, n, d;
+  int32_t canon, pad_;
+};
+struct ResidentPass {
+  const ResidentRow* rows;
+  const int32_t* out_pos;  // as PassArgs
+  const double2* ph;
+  const void* P;
+  const double2* diag;
+};
+constexpr int kResidentPasses = 32;  // distinct entries of a sequence
+// Passes [begin, end) of the sequence pass[0 .. nhead), the following nbody entries reps times, then
+// the ntail after them, on state X (gathered through in_pos: the first pass's order) into Y in the
+// last pass's output order; X and Y may be the same array.
+struct ResidentArgs {
+  ResidentPass pass[kResidentPasses];
+  int nhead = 0, nbody = 0, ntail = 0;
+  int64_t reps = 0, begin = 0, end = 0;
+  int N = 0, W = 0;
+  const int32_t* in_pos = nullptr;
+  const double2* X = nullptr;
+  double2* Y = nullptr;
+};
+constexpr int kResidentU = 6;  // propagator entries a lane loads together: 24 columns of the band
+// pair: a body of two passes, at most 256 rows, bands of at most kResidentU k-steps (not BF16x3)
+hipError_t launch_resident(hipStream_t s, int fmt, const ResidentArgs& a, bool pair);
 hipError_t launch_reduce(hipStream_t s, const ReduceArgs& a, int nblocks, double* mass, double* energy);
 // n copies of whole arrays in one launch (max_elems: the longest)
 struct CopyItem {
