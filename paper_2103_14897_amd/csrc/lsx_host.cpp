@@ -3270,9 +3270,16 @@ struct lsx_sampler {
   int p[2] = {0, 0};
   double eps = 0.0;
   int nf[2] = {0, 0};
-  int ntiles[2] = {0, 0};  // tiles of a pass over every fibre and column: the launch bound
-  DBuf<TileDesc> tiles[2];  // tiles of the sampled (fibre, column) pairs, built per sub-step
-  DBuf<int32_t> cols[2], ncols[2], off[2], fid[2], d0[2];
+  // W = 1: the launch bound (tiles of every fibre) and the tiles of the sampled fibres, per sub-step
+  int ntiles[2] = {0, 0};
+  DBuf<TileDesc> tiles[2];
+  DBuf<int32_t> off[2], fid[2], d0[2];
+  // W > 1: slots of the classes of fibres with one propagator (SlotBuild, SlotArgs)
+  int nunits[2] = {0, 0}, nclass[2] = {0, 0}, maxslots[2] = {0, 0};
+  DBuf<SlotUnit> units[2];
+  DBuf<int32_t> cols[2], ncols[2], qfib[2], cstart[2], clen[2], fcls[2], cn[2], sbase[2];
+  DBuf<int64_t> xbase[2];
+  DBuf<Slot> slot[2];
   DBuf<int64_t> poff[2];
   // band of every (fibre, 16-row block): [2 (bptr[f] + rb)] = k0, [.. + 1] = k1 (fibre positions)
   DBuf<int32_t> bptr[2], band[2];
@@ -3281,9 +3288,50 @@ struct lsx_sampler {
   DBuf<float> X, z;
 };
 
-// column block of the sampled passes: one 16-column block per tile (the sampled columns of
-// a fibre are typically few)
-static constexpr int kSampledNB = 1;
+// Static tables of a layer's sampled passes of several wavepackets: the classes of fibres that share
+// a stored propagator, and one unit per 16-row block of each.
+static lsx_status sampler_classes(lsx_sampler* sm, int j) {
+  const LayerDev& ld = sm->pl->L[j];
+  const int nf = ld.nf, W = sm->st->W, nc = ld.nunique;
+  std::vector<std::vector<int>> members(nc);
+  for (int f = 0; f < nf; ++f) members[ld.rep[f]].push_back(f);
+  std::vector<int32_t> qfib, cstart(1, 0), clen;
+  std::vector<SlotUnit> units;
+  for (int c = 0; c < nc; ++c) {
+    const int f0 = members[c][0], L = ld.h_ptr[f0 + 1] - ld.h_ptr[f0];
+    for (int f : members[c]) qfib.push_back(f);
+    cstart.push_back((int32_t)qfib.size());
+    clen.push_back(L);
+    for (int rb = 0; rb < (L + 15) / 16; ++rb) {
+      SlotUnit u;
+      u.poff = ld.h_poff[f0];
+      u.cls = c;
+      u.L = L;
+      u.rb = rb;
+      u.d0 = ld.h_d0[f0];
+      fibre_band(ld, f0, rb, 1, u.k0, u.k1);
+      units.push_back(u);
+    }
+  }
+  // longest first, so that the last workgroups to start are short
+  std::stable_sort(units.begin(), units.end(), [](const SlotUnit& x, const SlotUnit& y) { return x.L > y.L; });
+  sm->nunits[j] = (int)units.size();
+  sm->nclass[j] = nc;
+  // a wavepacket draws at most p fibres
+  for (const std::vector<int>& m : members)
+    sm->maxslots[j] = (int)std::max<int64_t>(sm->maxslots[j], (int64_t)std::min<int64_t>(m.size(), sm->p[j]) * W);
+  LSX_TRY(sm->units[j].upload(units, nullptr));
+  LSX_TRY(sm->qfib[j].upload(qfib, nullptr));
+  LSX_TRY(sm->cstart[j].upload(cstart, nullptr));
+  LSX_TRY(sm->clen[j].upload(clen, nullptr));
+  LSX_TRY(sm->fcls[j].upload(std::vector<int32_t>(ld.rep.begin(), ld.rep.end()), nullptr));
+  LSX_TRY(sm->cols[j].alloc((size_t)std::max(nf, 1) * W));
+  LSX_TRY(sm->ncols[j].alloc(std::max(nf, 1)));
+  LSX_TRY(sm->cn[j].alloc(std::max(nc, 1)));
+  LSX_TRY(sm->sbase[j].alloc(std::max(nc, 1)));
+  LSX_TRY(sm->xbase[j].alloc(std::max(nc, 1)));
+  return sm->slot[j].alloc((size_t)std::max(nf, 1) * W);
+}
 
 extern "C" lsx_status lsx_sampler_create(lsx_plan* pl, lsx_state* st, int32_t p1, int32_t p2, double eps,
                                          lsx_sampler** out) {
@@ -3312,14 +3360,12 @@ extern "C" lsx_status lsx_sampler_create(lsx_plan* pl, lsx_state* st, int32_t p1
     const int nf = ld.nf;
     sm->nf[j] = nf;
     maxnf = std::max(maxnf, nf);
-    const int nwb = (W + 16 * kSampledNB - 1) / (16 * kSampledNB);
     int64_t ntiles = 0;
-    for (int f = 0; f < nf; ++f) ntiles += (int64_t)((ld.h_ptr[f + 1] - ld.h_ptr[f] + 15) / 16) * nwb;
-    if (ntiles > INT32_MAX) return fail(LSX_E_INVALID, "too many tiles for one sampled pass");
+    for (int f = 0; f < nf; ++f) ntiles += (ld.h_ptr[f + 1] - ld.h_ptr[f] + 15) / 16;
+    if (ntiles * ((W + 15) / 16) > INT32_MAX) return fail(LSX_E_INVALID, "too many tiles for one sampled pass");
     sm->ntiles[j] = (int)ntiles;
-    LSX_TRY(sm->tiles[j].alloc((size_t)std::max<int64_t>(ntiles, 1)));
-    LSX_TRY(sm->cols[j].alloc((size_t)std::max(nf, 1) * W));
-    LSX_TRY(sm->ncols[j].alloc(std::max(nf, 1)));
+    if (W == 1) LSX_TRY(sm->tiles[j].alloc((size_t)std::max<int64_t>(ntiles, 1)));
+    else if (!ld.h_poff.empty()) LSX_TRY(sampler_classes(sm.get(), j));
     LSX_TRY(sm->off[j].alloc(std::max(nf, 1)));
     std::vector<int64_t> poff(nf, 0);
     std::vector<int32_t> d0(nf, 0);
@@ -3426,14 +3472,28 @@ lsx_status sampler_features(lsx_sampler* sm, int layer, float* X, hipStream_t s)
   return LSX_OK;
 }
 
-// one sampled sub-step of `layer` with propagators `half`, uniforms u [W][ustride]
-lsx_status sampled_substep(lsx_sampler* sm, int layer, int half, const double* u, int ustride, hipStream_t s) {
+lsx_status apply_phase(lsx_plan* pl, lsx_state* st, const double2* ph, hipStream_t s) {
+  if (!ph || pl->sys->N == 0) return LSX_OK;
+  LSX_HIP_TRY(launch_phase_apply(s, pl->sys->N, st->W, ph, st->buf[0]));
+  return LSX_OK;
+}
+
+// One sampled sub-step of `layer` with propagators `half`, uniforms u [W][ustride].  pend: phase the
+// stored state still lacks (null: none).  The sampled passes of several wavepackets multiply it into
+// the few columns they read and take it off what they write; the other passes apply it first (pend
+// is then null).
+lsx_status sampled_substep(lsx_sampler* sm, int layer, int half, const double* u, int ustride, const double2*& pend,
+                           hipStream_t s) {
   lsx_plan* pl = sm->pl;
   lsx_state* st = sm->st;
   const int j = layer - 1;
   const int W = st->W, nf = sm->nf[j];
   if (nf == 0) return LSX_OK;
   if (!pl->L[j].prop[half].present) return fail(LSX_E_INVALID, "plan holds no propagator for this sub-step");
+  if (sm->p[j] == 0 || W == 1) {
+    LSX_TRY(apply_phase(pl, st, pend, s));
+    pend = nullptr;
+  }
   if (sm->p[j] == 0) {  // fallback: the deterministic pass
     Runner r{pl, st, s};
     LSX_TRY(r.pass(layer, half, 0, -1));
@@ -3441,32 +3501,61 @@ lsx_status sampled_substep(lsx_sampler* sm, int layer, int half, const double* u
   }
   const float* z = nullptr;
   if (sm->mlp) {
-    LSX_TRY(sampler_features(sm, layer, sm->X.p, s));
+    LSX_TRY(sampler_features(sm, layer, sm->X.p, s));  // fibre masses: no phase enters
     LSX_HIP_TRY(launch_mlp_fwd(s, sm->mlp->theta.p, sm->mlp->nin, sm->X.p, (int64_t)W * nf, sm->z.p));
     z = sm->z.p;
   }
   LSX_HIP_TRY(launch_sample_weights(s, nf, W, sm->p[j], ustride, u, z, sm->eps, sm->wt[j].p));
   const LayerDev& ld = pl->L[j];
-  LSX_HIP_TRY(launch_sampled_tiles(s, nf, W, kSampledNB, sm->wt[j].p, ld.ptr.p, sm->poff[j].p, sm->d0[j].p,
-                                   sm->bptr[j].p, sm->band[j].p, sm->cols[j].p, sm->ncols[j].p, sm->off[j].p,
-                                   sm->tiles[j].p, sm->count.p + j));
-  PassArgs a = canon_pass_args(pl, st, layer, half);
-  a.tiles = sm->tiles[j].p;
-  a.tcount = sm->count.p + j;
-  a.wt = sm->wt[j].p;
-  a.cols = sm->cols[j].p;
-  a.ncols = sm->ncols[j].p;
-  // sampled tiles are per row block: a fibre-length split, never the row-split kernel
-  LSX_HIP_TRY(launch_pass(s, pl->fmt, W, sm->ntiles[j], kSampledNB, st->ks[j] > 0 ? st->ks[j] : 2, a));
-  LSX_HIP_TRY(launch_copy_cols(s, sm->ntiles[j], sm->tiles[j].p, sm->count.p + j, kSampledNB, canon_pos(pl, layer),
-                               W, sm->cols[j].p, sm->ncols[j].p, st->buf[1], st->buf[0]));
-  return LSX_OK;
-}
-
-lsx_status phase_canon(lsx_plan* pl, lsx_state* st, int half, hipStream_t s) {
-  if (pl->kappa == 0.0 || pl->sys->N == 0) return LSX_OK;
-  if (!pl->phase[half].p) return fail(LSX_E_INVALID, "plan holds no phase table for this slot");
-  LSX_HIP_TRY(launch_phase_apply(s, pl->sys->N, st->W, pl->phase[half].p, st->buf[0]));
+  if (W == 1) {
+    LSX_HIP_TRY(launch_sampled_tiles(s, nf, sm->wt[j].p, ld.ptr.p, sm->poff[j].p, sm->d0[j].p, sm->bptr[j].p,
+                                     sm->band[j].p, sm->off[j].p, sm->tiles[j].p, sm->count.p + j));
+    PassArgs a = canon_pass_args(pl, st, layer, half);
+    a.tiles = sm->tiles[j].p;
+    a.tcount = sm->count.p + j;
+    a.wt = sm->wt[j].p;
+    LSX_HIP_TRY(launch_pass(s, pl->fmt, W, sm->ntiles[j], 1, st->ks[j] > 0 ? st->ks[j] : 2, a));
+    LSX_HIP_TRY(launch_copy_rows(s, sm->ntiles[j], sm->tiles[j].p, sm->count.p + j, canon_pos(pl, layer), st->buf[1],
+                                 st->buf[0]));
+    return LSX_OK;
+  }
+  SlotBuild b;
+  b.nf = nf;
+  b.nc = sm->nclass[j];
+  b.W = W;
+  b.wt = sm->wt[j].p;
+  b.ptr = ld.ptr.p;
+  b.qfib = sm->qfib[j].p;
+  b.cstart = sm->cstart[j].p;
+  b.clen = sm->clen[j].p;
+  b.fcls = sm->fcls[j].p;
+  b.pos = canon_pos(pl, layer);
+  b.pend = pend;
+  b.X = st->buf[0];
+  b.cols = sm->cols[j].p;
+  b.ncols = sm->ncols[j].p;
+  b.off = sm->off[j].p;
+  b.n = sm->cn[j].p;
+  b.xbase = sm->xbase[j].p;
+  b.sbase = sm->sbase[j].p;
+  b.slot = sm->slot[j].p;
+  b.Xc = st->buf[1];  // at most every fibre's every column: the state's size
+  LSX_HIP_TRY(launch_slots(s, b));
+  SlotArgs a;
+  a.units = sm->units[j].p;
+  a.n = b.n;
+  a.xbase = b.xbase;
+  a.sbase = b.sbase;
+  a.slot = b.slot;
+  a.Xc = b.Xc;
+  a.Y = st->buf[0];
+  a.pos = b.pos;
+  a.pend = pend;
+  a.P = ld.prop[half].data.p;
+  a.diag = pl->diag.p ? pl->diag.p + (size_t)((layer - 1) * 3 + half) * pl->sys->N : nullptr;
+  a.zero = pl->zero.p;
+  a.W = W;
+  LSX_HIP_TRY(launch_pass_slots(s, pl->fmt, sm->nunits[j], sm->maxslots[j], a));
   return LSX_OK;
 }
 
@@ -3526,22 +3615,31 @@ extern "C" lsx_status lsx_ss_step(lsx_sampler* sm, const double* u, int64_t nste
   if (pl->scheme == LSX_YOSHIDA4) return fail(LSX_E_INVALID, "stochastic steps take Lie or Strang schemes");
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const bool strang = scheme_strang(pl->scheme);
-  // (layer, propagator half, phase half after it or -1)
+  // (layer, propagator half).  A sampled pass touches a few columns of each fibre, so the kinetic
+  // phases between a step's sub-steps stay pending and the whole state is multiplied once, at the end.
   struct Sub {
-    int layer, half, ph;
+    int layer, half;
   };
-  const Sub lie[2] = {{1, 0, 0}, {2, 0, -1}};
-  const Sub str[3] = {{1, 1, 1}, {2, 0, 1}, {1, 1, -1}};
+  const Sub lie[2] = {{1, 0}, {2, 0}};
+  const Sub str[3] = {{1, 1}, {2, 0}, {1, 1}};
   const Sub* subs = strang ? str : lie;
   const int nsub = strang ? 3 : 2;
   const int W = sm->st->W, pmax = std::max(1, std::max(sm->p[0], sm->p[1]));
   const int64_t per = (int64_t)W * pmax;
-  for (int64_t k = 0; k < nsteps; ++k)
+  const bool phases = pl->kappa != 0.0 && pl->sys->N > 0;
+  for (int h = 0; h <= (strang ? 1 : 0); ++h)
+    if (phases && !pl->phase[h].p) return fail(LSX_E_INVALID, "plan holds no phase table for this slot");
+  for (int64_t k = 0; k < nsteps; ++k) {
+    const double2* pend = nullptr;
     for (int i = 0; i < nsub; ++i) {
       const double* uk = u ? u + (k * nsub + i) * per : nullptr;
-      LSX_TRY(sampled_substep(sm, subs[i].layer, subs[i].half, uk, pmax, s));
-      if (subs[i].ph >= 0) LSX_TRY(phase_canon(pl, sm->st, subs[i].ph, s));
+      LSX_TRY(sampled_substep(sm, subs[i].layer, subs[i].half, uk, pmax, pend, s));
+      // the phase after this sub-step, together with one that is pending: Strang's half (slot 1),
+      // its two halves or Lie's whole (slot 0)
+      if (phases && i + 1 < nsub) pend = pl->phase[strang && !pend ? 1 : 0].p;
     }
+    LSX_TRY(apply_phase(pl, sm->st, pend, s));
+  }
   return LSX_OK;
 }
 

@@ -86,8 +86,8 @@ struct PassArgs;
 // Arguments of every fibre-pass kernel.  Element k of fibre f (fibre position
 // p = r0 + k) is row in_pos[p] of X and row out_pos[p] of Y (identity when null),
 // so a pass can read one array layout and write another.
-// Weighted passes (wt set): the output is x + wt[f][w] (P_f x - x) per fibre f and column
-// w, i.e. a weighted fibre increment; tcount (device) bounds the tiles a launch runs.
+// Weighted single-state passes (wt set): the output is x + wt[f] (P_f x - x) per fibre f, i.e. a
+// weighted fibre increment; tcount (device) bounds the tiles a launch runs.
 struct PassArgs {
   const TileDesc* tiles = nullptr;
   const int32_t* in_pos = nullptr;
@@ -100,12 +100,8 @@ struct PassArgs {
   double2* Y = nullptr;             // output state [rows][W]
   const void* zero = nullptr;       // >= 256 zero bytes: target of every out-of-range operand load
   const PassArgs* batch = nullptr;  // batched launches: per-system arguments, indexed by TileDesc::f
-  const double* wt = nullptr;       // weighted passes: [fibre][W] increment weights
+  const double* wt = nullptr;       // weighted single-state passes: [fibre] increment weights
   const int32_t* tcount = nullptr;  // device tile count: workgroups at or past it exit
-  // column-gathered passes: column slot s of fibre f is state column cols[f][s] for
-  // s < ncols[f] (TileDesc::wb then counts blocks of 16 NB slots, not of columns)
-  const int32_t* cols = nullptr;
-  const int32_t* ncols = nullptr;
   // row-split passes: band of every 16-row block of the layer's stored propagators, (k0, k1)
   // fibre positions at [2 (TileDesc::bb + block)]; each wave of a tile then skips the chunks
   // outside its own block's band (null: the tile's band for every wave)
@@ -178,6 +174,35 @@ hipError_t launch_phase_table(hipStream_t s, int64_t N, const double* K2, double
 hipError_t launch_phase_apply(hipStream_t s, int64_t N, int W, const double2* ph, double2* c);
 hipError_t launch_pass(hipStream_t s, int fmt, int W, int ntiles, int nb, int ksplit, const PassArgs& a,
                        bool batched = false);
+// Sampled passes of several wavepackets (k_pass_slots).  The drawn (fibre, wavepacket) pairs of all
+// fibres that share a stored propagator are its class's slots; their columns lie compacted in Xc,
+// class c as [L][n[c]] at xbase[c], slot s with its fibre's first position, wavepacket and weight at
+// slot[sbase[c] + s].  A unit is one 16-row block of one class's propagator.
+struct SlotUnit {
+  int64_t poff;
+  int32_t cls, L, rb, d0, k0, k1;  // k0, k1 as TileDesc
+};
+struct Slot {
+  int32_t r0, w;
+  double g;
+};
+struct SlotArgs {
+  const SlotUnit* units = nullptr;
+  const int32_t* n = nullptr;
+  const int64_t* xbase = nullptr;
+  const int32_t* sbase = nullptr;
+  const Slot* slot = nullptr;
+  const double2* Xc = nullptr;
+  double2* Y = nullptr;             // the state [rows][W], canonical order, updated in place
+  const int32_t* pos = nullptr;     // canonical index of a fibre position (identity when null)
+  const double2* pend = nullptr;    // pending phase: the state's true value is pend[row] times the stored one
+  const void* P = nullptr;
+  const double2* diag = nullptr;
+  const void* zero = nullptr;
+  int W = 0;
+};
+// max_slots: most slots a class can have
+hipError_t launch_pass_slots(hipStream_t s, int fmt, int nunits, int max_slots, const SlotArgs& a);
 // row-split tiles (lsx_rowsplit.hip): ms waves on consecutive row blocks of 16 nb columns
 hipError_t launch_rowsplit(hipStream_t s, int fmt, int ntiles, int nb, int ms, const PassArgs& a);
 // Batched launches with a.persist set: computes (once per kernel) the persistent grid of the pass
@@ -275,14 +300,38 @@ hipError_t launch_si_step(hipStream_t s, const Sweep& sweep, int W, double tau, 
 hipError_t launch_subset_weights(hipStream_t s, int nf, int W, int p, int ustride, const double* u, double* wt);
 hipError_t launch_sample_weights(hipStream_t s, int nf, int W, int p, int ustride, const double* u, const float* z,
                                  double eps, double* wt);
-// column lists of the sampled fibres and their tiles (16 NB column slots per tile)
+// single-state sampled passes: tiles of the sampled fibres
 // bptr, band (nullable): band of fibre f's row block rb at band[2 (bptr[f] + rb)] (k0, then k1)
-hipError_t launch_sampled_tiles(hipStream_t s, int nf, int W, int NB, const double* wt, const int32_t* ptr,
-                                const int64_t* poff, const int32_t* d0, const int32_t* bptr, const int32_t* band,
-                                int32_t* cols, int32_t* ncols, int32_t* off, TileDesc* tiles, int32_t* count);
-hipError_t launch_copy_cols(hipStream_t s, int ntiles, const TileDesc* tiles, const int32_t* count, int NB,
-                            const int32_t* pos, int W, const int32_t* cols, const int32_t* ncols, const double2* src,
-                            double2* dst);
+hipError_t launch_sampled_tiles(hipStream_t s, int nf, const double* wt, const int32_t* ptr, const int64_t* poff,
+                                const int32_t* d0, const int32_t* bptr, const int32_t* band, int32_t* off,
+                                TileDesc* tiles, int32_t* count);
+hipError_t launch_copy_rows(hipStream_t s, int ntiles, const TileDesc* tiles, const int32_t* count,
+                            const int32_t* pos, const double2* src, double2* dst);
+// Slots of the sampled fibres (SlotArgs): fibres in class order qfib, class c of them at
+// [cstart[c], cstart[c + 1]), its fibre length clen[c]; fcls: class of a fibre.  Fills the column
+// lists cols [nf][W] / ncols, the slot offset of every fibre inside its class (off), the class tables
+// n, xbase, sbase, the slots and the compacted columns Xc (times pend where set).
+struct SlotBuild {
+  int nf = 0, nc = 0, W = 0;
+  const double* wt = nullptr;
+  const int32_t* ptr = nullptr;
+  const int32_t* qfib = nullptr;
+  const int32_t* cstart = nullptr;
+  const int32_t* clen = nullptr;
+  const int32_t* fcls = nullptr;
+  const int32_t* pos = nullptr;
+  const double2* pend = nullptr;
+  const double2* X = nullptr;
+  int32_t* cols = nullptr;
+  int32_t* ncols = nullptr;
+  int32_t* off = nullptr;
+  int32_t* n = nullptr;
+  int64_t* xbase = nullptr;
+  int32_t* sbase = nullptr;
+  Slot* slot = nullptr;
+  double2* Xc = nullptr;
+};
+hipError_t launch_slots(hipStream_t s, const SlotBuild& b);
 hipError_t launch_fibre_incr(hipStream_t s, int nf, const int32_t* ptr, const int32_t* rows, int W,
                              const double2* X, const double2* Y, double* out);
 hipError_t launch_features(hipStream_t s, int nf, int W, int d, const double* sfeat, const double* mass,

@@ -176,7 +176,6 @@ __device__ __forceinline__ void k_pass_f64_tile(const PassArgs& a0, int ti, doub
 template <int NB, int KS, int U, bool GATHER, bool BATCH>
 __global__ LSX_MFMA_BOUNDS(64 * KS, NB < 4) void k_pass_f64(PassArgs a0) {
   extern __shared__ double red[];
-  if (a0.tcount && (int)blockIdx.x >= *a0.tcount) return;
   k_pass_f64_tile<NB, KS, U, GATHER, BATCH>(a0, blockIdx.x, red);
 }
 
@@ -235,7 +234,6 @@ __device__ __forceinline__ void k_pass_f32_tile(const PassArgs& a0, int ti, doub
 template <int NB, int KS, int U, bool GATHER, bool BATCH>
 __global__ LSX_MFMA_BOUNDS(64 * KS, NB * U < 16) void k_pass_f32(PassArgs a0) {
   extern __shared__ double red[];
-  if (a0.tcount && (int)blockIdx.x >= *a0.tcount) return;
   k_pass_f32_tile<NB, KS, U, GATHER, BATCH>(a0, blockIdx.x, red);
 }
 
@@ -344,7 +342,6 @@ __device__ __forceinline__ void k_pass_bf16x3_tile(const PassArgs& a0, int ti, d
 template <int NB, int KS, int U, bool GATHER, bool BATCH>
 __global__ LSX_MFMA_BOUNDS(64 * KS, NB == 1) void k_pass_bf16x3(PassArgs a0) {
   extern __shared__ double red[];
-  if (a0.tcount && (int)blockIdx.x >= *a0.tcount) return;
   k_pass_bf16x3_tile<NB, KS, U, GATHER, BATCH>(a0, blockIdx.x, red);
 }
 
@@ -352,6 +349,138 @@ template <int NB, int KS, int U, bool GATHER>
 __global__ LSX_MFMA_BOUNDS(64 * KS, NB == 1) void k_pass_bf16x3_persist(PassArgs a0) {
   extern __shared__ double red[];
   persistent_tiles(a0, [&](int ti) { k_pass_bf16x3_tile<NB, KS, U, GATHER, true>(a0, ti, red); });
+}
+
+// ---------------------------------------------------------------- sampled passes (W > 1)
+// Weighted fibre increments x + g (P_f x - x) of the drawn (fibre, wavepacket) pairs, from the
+// compacted columns of every class of fibres with one propagator (SlotArgs), written straight into
+// the state.  A workgroup takes one 16-row block of a class's propagator and all of the class's
+// slots, 32 at a time; its KS waves split the fibre length as in the passes above.
+// Bound by reading the propagators (253 MB twice at most, at 16 draws for each of 128 wavepackets of
+// the twisted bilayer, kappa = 1, N = 398821): 123 us a pass and 32 for the compaction.  Tiles of
+// single fibres read a shared propagator once per drawn fibre (889 fibres share 58 of them) for 2.3
+// drawn columns of 16 on average, on a grid sized for every fibre and column, and wrote a second
+// array that was copied back: 650 to 790 us and 330.
+template <int FMT, int KS>
+__global__ LSX_MFMA_BOUNDS(64 * KS, FMT != PF_BF16X3) void k_pass_slots(SlotArgs a) {
+  constexpr int NB = 2, U = 2;
+  extern __shared__ double red[];
+  const SlotUnit t = a.units[blockIdx.x];
+  const int n = a.n[t.cls], L = t.L;
+  const int64_t xb = a.xbase[t.cls];
+  const Slot* slots = a.slot + a.sbase[t.cls];
+  PassArgs pa;
+  pa.X = a.Xc + xb;
+  pa.zero = a.zero;
+  pa.W = n;
+  TileDesc td;
+  td.k0 = t.k0;
+  td.k1 = t.k1;
+  const int lane = threadIdx.x & 63, kw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  const char* Pb = reinterpret_cast<const char*>(a.P) + t.poff;
+  for (int s0 = 16 * NB * blockIdx.y; s0 < n; s0 += 16 * NB * gridDim.y) {
+    int wc[NB];
+    bool wok[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      wc[nb] = s0 + 16 * nb + li;
+      wok[nb] = wc[nb] < n;
+    }
+    double acc[NB][2][4];
+    if constexpr (FMT == PF_BF16X3) {
+      const int nkc = ((L + 31) & ~31) >> 5;
+      const v8u16* P = reinterpret_cast<const v8u16*>(Pb) + (int64_t)t.rb * nkc * 6 * 64 + lane;
+      v4f rr[NB], ii[NB], ri[NB], ir[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) rr[nb] = ii[nb] = ri[nb] = ir[nb] = (v4f){0.f, 0.f, 0.f, 0.f};
+      int klo, khi;
+      tile_band(td, 32 * nkc, 32, klo, khi);
+      for (int kc = klo + kw; kc < khi; kc += KS) {
+        ChunkBF<NB> C;
+        load_chunk_bf<false>(C, pa, P, kc, khi, 0, L, lk, wc, wok);
+        mma_chunk_bf(rr, ii, ri, ir, C);
+      }
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          acc[nb][0][r] = (double)rr[nb][r] - (double)ii[nb][r];
+          acc[nb][1][r] = (double)ri[nb][r] + (double)ir[nb][r];
+        }
+    } else {
+      using PT = typename std::conditional<FMT == PF_F64, double2, float2>::type;
+      using V = typename std::conditional<FMT == PF_F64, v4d, v4f>::type;
+      const int nks = ((L + 15) & ~15) >> 2;
+      const PT* P = reinterpret_cast<const PT*>(Pb) + (int64_t)t.rb * nks * 64 + lane;
+      V k1[NB], k2[NB], k3[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) k1[nb] = k2[nb] = k3[nb] = (V){0, 0, 0, 0};
+      int klo, khi;
+      tile_band(td, 4 * nks, 4, klo, khi);
+      Group4<PT, NB, U> A, B;
+      const int stride = KS * U;
+      auto mma = [&](const Group4<PT, NB, U>& G) {
+        if constexpr (FMT == PF_F64) mma_group_f64(k1, k2, k3, G);
+        else mma_group_f32(k1, k2, k3, G);
+      };
+      int g = klo + kw * U;
+      load_group4<false>(A, pa, P, g, khi, 0, L, lk, wc, wok);
+      for (; g < khi; g += 2 * stride) {
+        load_group4<false>(B, pa, P, g + stride, khi, 0, L, lk, wc, wok);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(A);
+        if (g + stride >= khi) break;
+        load_group4<false>(A, pa, P, g + 2 * stride, khi, 0, L, lk, wc, wok);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(B);
+      }
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          acc[nb][0][r] = (double)k1[nb][r] - (double)k3[nb][r];
+          acc[nb][1][r] = (double)k1[nb][r] + (double)k2[nb][r];
+        }
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[(((kw * NB + nb) * 2 + c) * 4 + r) * 64 + lane] = acc[nb][c][r];
+    __syncthreads();
+    for (int r = kw; r < 4; r += KS) {
+      const int arow = 16 * t.rb + (FMT == PF_F64 ? 4 * r + lk : 4 * lk + r);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        if (arow >= L || !wok[nb]) continue;
+        double yr = 0.0, yi = 0.0;
+        for (int j = 0; j < KS; ++j) {
+          yr += red[(((j * NB + nb) * 2 + 0) * 4 + r) * 64 + lane];
+          yi += red[(((j * NB + nb) * 2 + 1) * 4 + r) * 64 + lane];
+        }
+        const double2 x = pa.X[(int64_t)arow * n + wc[nb]];
+        if (FMT != PF_F64) {
+          const double2 dg = a.diag[t.d0 + arow];
+          yr += dg.x * x.x - dg.y * x.y;
+          yi += dg.x * x.y + dg.y * x.x;
+        }
+        const Slot sl = slots[wc[nb]];
+        yr = x.x + sl.g * (yr - x.x);
+        yi = x.y + sl.g * (yi - x.y);
+        const int64_t row = a.pos ? a.pos[sl.r0 + arow] : sl.r0 + arow;
+        if (a.pend) {  // the stored value: the true one with the pending phase taken off
+          const double2 h = a.pend[row];
+          const double zr = h.x * yr + h.y * yi;
+          yi = h.x * yi - h.y * yr;
+          yr = zr;
+        }
+        a.Y[row * a.W + sl.w] = make_double2(yr, yi);
+      }
+    }
+    __syncthreads();  // the LDS is free again
+  }
 }
 
 // ---------------------------------------------------------------- single-state fibre pass (W = 1)
@@ -840,6 +969,24 @@ template <int NB, int KS>
 static hipError_t launch_mfma(hipStream_t s, int fmt, int ntiles, const PassArgs& a, bool batched, bool gather) {
   return gather ? launch_mfma_g<NB, KS, true>(s, fmt, ntiles, a, batched)
                 : launch_mfma_g<NB, KS, false>(s, fmt, ntiles, a, batched);
+}
+
+hipError_t launch_pass_slots(hipStream_t s, int fmt, int nunits, int max_slots, const SlotArgs& a) {
+  if (nunits == 0) return hipSuccess;
+  constexpr int KS = 4, NB = 2;
+  const size_t shm = (size_t)KS * NB * 2 * 4 * 64 * sizeof(double);
+  // few classes of many slots: their 32-slot blocks go to workgroups of their own, up to 16
+  // workgroups a compute unit (1660 units, up to 2048 slots: 138 us a pass with one workgroup a unit,
+  // 123 with two); with many classes a class has few slots and one workgroup takes them
+  const int64_t want = std::max(1, 4096 / nunits), most = ((int64_t)max_slots + 16 * NB - 1) / (16 * NB);
+  const dim3 g(nunits, (unsigned)std::max<int64_t>(1, std::min(want, most)));
+  if (fmt == PF_F64)
+    hipLaunchKernelGGL((k_pass_slots<PF_F64, KS>), g, dim3(64 * KS), shm, s, a);
+  else if (fmt == PF_F32)
+    hipLaunchKernelGGL((k_pass_slots<PF_F32, KS>), g, dim3(64 * KS), shm, s, a);
+  else
+    hipLaunchKernelGGL((k_pass_slots<PF_BF16X3, KS>), g, dim3(64 * KS), shm, s, a);
+  return hipGetLastError();
 }
 
 template <int KS, bool B>

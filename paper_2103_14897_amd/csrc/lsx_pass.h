@@ -54,18 +54,15 @@ __device__ __forceinline__ void split3f(float x, unsigned short& t0, unsigned sh
 }
 
 // ---------------------------------------------------------------- tile columns
-// State column of this lane's slot in each of the tile's NB column blocks (slot
-// (wb NB + nb) 16 + lane % 16), and whether it exists.  Column-gathered passes look the
-// slot up in the fibre's column list.
+// State column of this lane in each of the tile's NB column blocks ((wb NB + nb) 16 + lane % 16),
+// and whether it exists.
 template <int NB>
 __device__ __forceinline__ void tile_cols(const PassArgs& a, const TileDesc& t, int li, int (&wc)[NB],
                                           bool (&wok)[NB]) {
-  const int nc = a.cols ? a.ncols[t.f] : a.W;
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
-    const int sl = (t.wb * NB + nb) * 16 + li;
-    wok[nb] = sl < nc;
-    wc[nb] = a.cols ? (wok[nb] ? a.cols[(int64_t)t.f * a.W + sl] : 0) : sl;
+    wc[nb] = (t.wb * NB + nb) * 16 + li;
+    wok[nb] = wc[nb] < a.W;
   }
 }
 
@@ -119,18 +116,11 @@ __device__ __forceinline__ void pass_epilogue(const PassArgs& a, const TileDesc&
         yr = acc[nb][0][r];
         yi = acc[nb][1][r];
       }
-      if (MIX || a.wt) {
+      if (MIX) {
         const double2 x = a.X[irow * W + w];
-        if (MIX) {
-          const double2 dg = a.diag[t.d0 + arow];
-          yr += dg.x * x.x - dg.y * x.y;
-          yi += dg.x * x.y + dg.y * x.x;
-        }
-        if (a.wt) {
-          const double g = a.wt[(int64_t)t.f * W + w];
-          yr = x.x + g * (yr - x.x);
-          yi = x.y + g * (yi - x.y);
-        }
+        const double2 dg = a.diag[t.d0 + arow];
+        yr += dg.x * x.x - dg.y * x.y;
+        yi += dg.x * x.y + dg.y * x.x;
       }
       if (a.ph) {
         const double zr = ph.x * yr - ph.y * yi;

@@ -63,7 +63,6 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f32m(PassArgs a) {
   using SM = StageMap<NB, MS>;
   constexpr int KC = SM::KC;
   __shared__ float4 xs[2][SM::CR][SM::CW];
-  if (a.tcount && (int)blockIdx.x >= *a.tcount) return;
   const TileDesc t0 = a.tiles[blockIdx.x];
   if (t0.f < 0) return;
   const int r0 = t0.r0, L = t0.L;
@@ -85,14 +84,8 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f32m(PassArgs a) {
   tile_cols<NB>(a, t, li, wc, wok);
   // this thread's staging slot: column c (fixed), rows rr0 + j RSTEP of each chunk
   const int c = threadIdx.x % SM::CW, rr0 = threadIdx.x / SM::CW;
-  int sw;
-  bool sok;
-  {
-    const int nc = a.cols ? a.ncols[t.f] : a.W;
-    const int sl = t.wb * SM::CW + c;
-    sok = sl < nc;
-    sw = a.cols ? (sok ? a.cols[(int64_t)t.f * a.W + sl] : 0) : sl;
-  }
+  const int sw = t.wb * SM::CW + c;
+  const bool sok = sw < a.W;
   v4f k1[NB], k2[NB], k3[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) k1[nb] = k2[nb] = k3[nb] = (v4f){0.f, 0.f, 0.f, 0.f};
@@ -324,7 +317,6 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_bf16m(PassArgs a) {
   constexpr int PER = 32 * CW / (64 * MS), RSTEP = 64 * MS / CW;
   constexpr int RP = PER > 1 ? 2 : 1;  // consecutive rows a thread stages together
   __shared__ __attribute__((aligned(16))) unsigned short xb[2][6][NB][64][8];
-  if (a.tcount && (int)blockIdx.x >= *a.tcount) return;
   const TileDesc t0 = a.tiles[blockIdx.x];
   if (t0.f < 0) return;
   const int r0 = t0.r0, L = t0.L;
@@ -341,14 +333,8 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_bf16m(PassArgs a) {
   bool wok[NB];
   tile_cols<NB>(a, t, li, wc, wok);
   const int c = threadIdx.x % CW, rr0 = threadIdx.x / CW;
-  int sw;
-  bool sok;
-  {
-    const int nc = a.cols ? a.ncols[t.f] : a.W;
-    const int sl = t.wb * CW + c;
-    sok = sl < nc;
-    sw = a.cols ? (sok ? a.cols[(int64_t)t.f * a.W + sl] : 0) : sl;
-  }
+  const int sw = t.wb * CW + c;
+  const bool sok = sw < a.W;
   v4f rr[NB], ii[NB], ri[NB], ir[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) rr[nb] = ii[nb] = ri[nb] = ir[nb] = (v4f){0.f, 0.f, 0.f, 0.f};

@@ -183,9 +183,25 @@ __global__ __launch_bounds__(256) void k_sample_weights(int nf, int W, int p, in
   }
   for (int f = threadIdx.x; f < nf; f += blockDim.x) acc[f] = 0.0;
   __syncthreads();
+  // Summed in fibre order by one thread, which fixes every draw.  Sixteen entries are read before
+  // they are added: with one read and one write an entry, the LDS latency of each was the kernel's
+  // time (889 fibres, 128 wavepackets: 39 us, now 19).
   if (threadIdx.x == 0) {
     double c = 0.0;
-    for (int f = 0; f < nf; ++f) {
+    int f = 0;
+    for (; f + 16 <= nf; f += 16) {
+      double v[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] = q[f + i];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        c += v[i];
+        v[i] = c;
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) cdf[f + i] = v[i];
+    }
+    for (; f < nf; ++f) {
       c += q[f];
       cdf[f] = c;
     }
@@ -227,18 +243,101 @@ __global__ __launch_bounds__(256) void k_fibre_cols(int nf, int W, const double*
   if (lane == 0) ncols[f] = base;
 }
 
-// Tile offsets of the sampled fibres: fibre f needs ceil(L_f / 16) row blocks times
-// ceil(ncols_f / (16 NB)) column-slot blocks; off = exclusive scan in fibre order.
-// One workgroup of 1024 threads; thread t scans fibres [t chunk, (t + 1) chunk).
-__global__ __launch_bounds__(1024) void k_scan_tiles(int nf, int NB, const int32_t* ptr, const int32_t* ncols,
-                                                     int32_t* off, int32_t* count) {
+// Slots of the classes (SlotBuild): the fibres' column counts summed in class order give every
+// fibre's slot offset inside its class and the class sizes; class sizes times fibre lengths summed
+// over the classes give the places of the compacted columns.  One workgroup of 1024 threads, dynamic
+// LDS (nf + 1) int32.
+__global__ __launch_bounds__(1024) void k_slot_scan(SlotBuild b) {
+  extern __shared__ int32_t S[];  // S[q]: slots before fibre qfib[q]
+  __shared__ int64_t scan[1024];
+  const int t = threadIdx.x;
+  auto block_scan = [&](int64_t mine) {  // exclusive sum over the threads
+    scan[t] = mine;
+    __syncthreads();
+    for (int o = 1; o < 1024; o <<= 1) {
+      const int64_t v = t >= o ? scan[t - o] : 0;
+      __syncthreads();
+      scan[t] += v;
+      __syncthreads();
+    }
+    const int64_t before = scan[t] - mine;
+    __syncthreads();
+    return before;
+  };
+  const int fc = (b.nf + 1023) / 1024, q0 = min(b.nf, t * fc), q1 = min(b.nf, q0 + fc);
+  int mine = 0;
+  for (int q = q0; q < q1; ++q) mine += b.ncols[b.qfib[q]];
+  int at = (int)block_scan(mine);
+  for (int q = q0; q < q1; ++q) {
+    S[q] = at;
+    at += b.ncols[b.qfib[q]];
+  }
+  if (q1 == b.nf) S[b.nf] = at;  // every thread past the end has the same sum
+  __syncthreads();
+  for (int q = q0; q < q1; ++q) b.off[b.qfib[q]] = S[q] - S[b.cstart[b.fcls[b.qfib[q]]]];
+  const int cc = (b.nc + 1023) / 1024, c0 = min(b.nc, t * cc), c1 = min(b.nc, c0 + cc);
+  int64_t elems = 0;
+  for (int c = c0; c < c1; ++c) elems += (int64_t)b.clen[c] * (S[b.cstart[c + 1]] - S[b.cstart[c]]);
+  int64_t xat = block_scan(elems);
+  for (int c = c0; c < c1; ++c) {
+    const int n = S[b.cstart[c + 1]] - S[b.cstart[c]];
+    b.n[c] = n;
+    b.sbase[c] = S[b.cstart[c]];
+    b.xbase[c] = xat;
+    xat += (int64_t)b.clen[c] * n;
+  }
+}
+
+// Compacted columns and slots of fibre f = blockIdx.x; workgroup y takes every gridDim.y-th share of
+// its elements, so that the reads of a fibre (one 16-byte entry per row and drawn wavepacket, each in
+// a line of its own) are in flight together (889 fibres, 2048 drawn pairs: 42 us with one, 32 with four).
+__global__ __launch_bounds__(256) void k_slot_gather(SlotBuild b) {
+  const int f = blockIdx.x, nc = b.ncols[f];
+  if (nc == 0) return;
+  const int c = b.fcls[f], n = b.n[c], off = b.off[f];
+  const int r0 = b.ptr[f], L = b.ptr[f + 1] - r0;
+  const int32_t* cols = b.cols + (int64_t)f * b.W;
+  if (blockIdx.y == 0)
+    for (int s = threadIdx.x; s < nc; s += blockDim.x) {
+      Slot sl;
+      sl.r0 = r0;
+      sl.w = cols[s];
+      sl.g = b.wt[(int64_t)f * b.W + sl.w];
+      b.slot[b.sbase[c] + off + s] = sl;
+    }
+  double2* out = b.Xc + b.xbase[c] + off;
+  // thread t takes elements t, t + nt, ... of the [L][nc] block, stepping (row, slot) along
+  const int t = blockIdx.y * blockDim.x + threadIdx.x, nt = gridDim.y * blockDim.x;
+  const int dk = nt / nc, ds = nt - dk * nc;
+  int s = t % nc;
+  for (int k = t / nc; k < L;) {
+    const int64_t row = b.pos ? b.pos[r0 + k] : r0 + k;
+    double2 x = b.X[row * b.W + cols[s]];
+    if (b.pend) {
+      const double2 h = b.pend[row];
+      x = make_double2(h.x * x.x - h.y * x.y, h.x * x.y + h.y * x.x);
+    }
+    out[(int64_t)k * n + s] = x;
+    k += dk;
+    s += ds;
+    if (s >= nc) {
+      s -= nc;
+      ++k;
+    }
+  }
+}
+
+// Tile offsets of a single state's sampled fibres (weight nonzero): ceil(L_f / 16) row blocks
+// each; off = exclusive scan in fibre order.  One workgroup of 1024 threads; thread t scans fibres
+// [t chunk, (t + 1) chunk).
+__global__ __launch_bounds__(1024) void k_scan_tiles(int nf, const double* wt, const int32_t* ptr, int32_t* off,
+                                                     int32_t* count) {
   __shared__ int32_t scan[1024];
   const int t = threadIdx.x;
   const int chunk = (nf + 1023) / 1024;
   const int f0 = min(nf, t * chunk), f1 = min(nf, f0 + chunk);
-  const int cw = 16 * NB;
   int mine = 0;
-  for (int f = f0; f < f1; ++f) mine += ((ptr[f + 1] - ptr[f] + 15) / 16) * ((ncols[f] + cw - 1) / cw);
+  for (int f = f0; f < f1; ++f) mine += wt[f] != 0.0 ? (ptr[f + 1] - ptr[f] + 15) / 16 : 0;
   scan[t] = mine;
   __syncthreads();
   for (int o = 1; o < 1024; o <<= 1) {  // inclusive Hillis-Steele scan
@@ -250,27 +349,26 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(int nf, int NB, const int32
   int pos = scan[t] - mine;
   for (int f = f0; f < f1; ++f) {
     off[f] = pos;
-    pos += ((ptr[f + 1] - ptr[f] + 15) / 16) * ((ncols[f] + cw - 1) / cw);
+    pos += wt[f] != 0.0 ? (ptr[f + 1] - ptr[f] + 15) / 16 : 0;
   }
   if (t == 1023) *count = scan[1023];
 }
 
-// Tiles of fibre f = blockIdx.x at off[f]: (row block rb, column-slot block cb), rb major, each with
-// its row block's band when the band table is given (else the whole fibre).
-__global__ __launch_bounds__(256) void k_emit_tiles(int NB, const int32_t* ptr, const int64_t* poff,
-                                                    const int32_t* d0, const int32_t* bptr, const int32_t* band,
-                                                    const int32_t* ncols, const int32_t* off, TileDesc* out) {
+// Tiles of sampled fibre f = blockIdx.x at off[f], one per row block, each with its row block's
+// band when the band table is given (else the whole fibre).
+__global__ __launch_bounds__(64) void k_emit_tiles(const double* wt, const int32_t* ptr, const int64_t* poff,
+                                                   const int32_t* d0, const int32_t* bptr, const int32_t* band,
+                                                   const int32_t* off, TileDesc* out) {
   const int f = blockIdx.x;
+  if (wt[f] == 0.0) return;
   const int r0 = ptr[f], L = ptr[f + 1] - r0;
-  const int cw = 16 * NB;
-  const int nc = (ncols[f] + cw - 1) / cw;
-  const int n = ((L + 15) / 16) * nc;
+  const int n = (L + 15) / 16;
   for (int k = threadIdx.x; k < n; k += blockDim.x) {
     TileDesc t;
     t.r0 = r0;
     t.L = L;
-    t.rb = k / nc;
-    t.wb = k - t.rb * nc;
+    t.rb = k;
+    t.wb = 0;
     t.poff = poff ? poff[f] : 0;
     t.f = f;
     t.d0 = d0 ? d0[f] : r0;
@@ -282,24 +380,17 @@ __global__ __launch_bounds__(256) void k_emit_tiles(int NB, const int32_t* ptr, 
   }
 }
 
-// Copies the (rows x gathered columns) block of every listed tile from src to dst (rows
-// through pos when set); tiles at or past *count are skipped.  256 threads per tile.
-__global__ __launch_bounds__(256) void k_copy_cols(const TileDesc* tiles, const int32_t* count, int NB,
-                                                   const int32_t* pos, int W, const int32_t* cols,
-                                                   const int32_t* ncols, const double2* src, double2* dst) {
-  if ((int)blockIdx.x >= *count) return;
-  const TileDesc t = tiles[blockIdx.x];
-  const int rows = min(16, t.L - 16 * t.rb);
-  const int cw = 16 * NB;
-  const int s0 = t.wb * cw, ns = min(cw, ncols[t.f] - s0);
-  for (int e = threadIdx.x; e < rows * cw; e += blockDim.x) {
-    const int r = e / cw, c = e - r * cw;
-    if (c >= ns) continue;
-    const int w = cols[(int64_t)t.f * W + s0 + c];
-    const int p = t.r0 + 16 * t.rb + r;
-    const int64_t row = pos ? pos[p] : p;
-    dst[row * W + w] = src[row * W + w];
-  }
+// Copies the rows of every listed tile of a single state from src to dst (through pos when set);
+// tiles at or past *count are skipped.  16 threads per tile.
+__global__ __launch_bounds__(256) void k_copy_rows(const TileDesc* tiles, const int32_t* count, const int32_t* pos,
+                                                   const double2* src, double2* dst) {
+  const int ti = blockIdx.x * 16 + (threadIdx.x >> 4);
+  if (ti >= *count) return;
+  const TileDesc t = tiles[ti];
+  const int a = 16 * t.rb + (threadIdx.x & 15);
+  if (a >= t.L) return;
+  const int64_t row = pos ? pos[t.r0 + a] : t.r0 + a;
+  dst[row] = src[row];
 }
 
 // ---------------------------------------------------------------- training data
@@ -778,25 +869,33 @@ hipError_t launch_sample_weights(hipStream_t s, int nf, int W, int p, int ustrid
   return hipGetLastError();
 }
 
-hipError_t launch_sampled_tiles(hipStream_t s, int nf, int W, int NB, const double* wt, const int32_t* ptr,
-                                const int64_t* poff, const int32_t* d0, const int32_t* bptr, const int32_t* band,
-                                int32_t* cols, int32_t* ncols, int32_t* off, TileDesc* tiles, int32_t* count) {
-  if (nf == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fibre_cols, dim3((nf + 3) / 4), dim3(256), 0, s, nf, W, wt, cols, ncols);
+hipError_t launch_slots(hipStream_t s, const SlotBuild& b) {
+  if (b.nf == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_fibre_cols, dim3((b.nf + 3) / 4), dim3(256), 0, s, b.nf, b.W, b.wt, b.cols, b.ncols);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, s, nf, NB, ptr, ncols, off, count);
+  hipLaunchKernelGGL(k_slot_scan, dim3(1), dim3(1024), (size_t)(b.nf + 1) * sizeof(int32_t), s, b);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_emit_tiles, dim3(nf), dim3(256), 0, s, NB, ptr, poff, d0, bptr, band, ncols, off, tiles);
+  hipLaunchKernelGGL(k_slot_gather, dim3(b.nf, 4), dim3(256), 0, s, b);
   return hipGetLastError();
 }
 
-hipError_t launch_copy_cols(hipStream_t s, int ntiles, const TileDesc* tiles, const int32_t* count, int NB,
-                            const int32_t* pos, int W, const int32_t* cols, const int32_t* ncols, const double2* src,
-                            double2* dst) {
+hipError_t launch_sampled_tiles(hipStream_t s, int nf, const double* wt, const int32_t* ptr, const int64_t* poff,
+                                const int32_t* d0, const int32_t* bptr, const int32_t* band, int32_t* off,
+                                TileDesc* tiles, int32_t* count) {
+  if (nf == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, s, nf, wt, ptr, off, count);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_emit_tiles, dim3(nf), dim3(64), 0, s, wt, ptr, poff, d0, bptr, band, off, tiles);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_rows(hipStream_t s, int ntiles, const TileDesc* tiles, const int32_t* count,
+                            const int32_t* pos, const double2* src, double2* dst) {
   if (ntiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_copy_cols, dim3(ntiles), dim3(256), 0, s, tiles, count, NB, pos, W, cols, ncols, src, dst);
+  hipLaunchKernelGGL(k_copy_rows, dim3((ntiles + 15) / 16), dim3(256), 0, s, tiles, count, pos, src, dst);
   return hipGetLastError();
 }
 
