@@ -921,8 +921,13 @@ static void plan_orders(lsx_plan* pl, bool use_sym) {
   }
 }
 
-// Fibres longer than this many rows (after the complex embedding) take the blocked solver.
-static constexpr int kBlockedMin = 96;
+// Matrices of more than this many rows (after the complex embedding) take the blocked solver, which
+// pads them to a multiple of 32 and runs in launches of a round each; the scalar one takes a single
+// launch and a workgroup a matrix.  Where a layer has longer ones, the short ones go through the
+// rounds that are launched anyway (twisted bilayer, N = 82321, plan: 42.0 ms with a line at 96 rows,
+// 37.9 at 32; N = 9061: 13.3 and 7.8); a layer without any stays scalar up to 64 rows (chain, N =
+// 1281: 1.8 ms, 2.1 in rounds).
+static constexpr int kBlockedMin = 32, kBlockedOnlyMin = 64;
 
 // Blocked two-sided Jacobi (see lsx_kernels.hip) of the matrices `sel` of a precompute batch:
 // sweeps of round-robin block rounds until a sweep rotates nothing, at most maxsweeps; the
@@ -936,12 +941,13 @@ static lsx_status block_jacobi(hipStream_t s, const std::vector<int32_t>& sel, c
   std::stable_sort(act.begin(), act.end(), [&](int x, int y) { return ndim[x] > ndim[y]; });
   int64_t qsize = 0;
   for (int m : act) qsize += (int64_t)(ndim[m] / 32) * 1024;
-  DBuf<int32_t> d_sel, d_mat, d_pp, d_pt, d_flag;
+  DBuf<int32_t> d_sel, d_mat, d_pp, d_flag, d_rot;
   DBuf<double> d_tiny, d_Q;
   LSX_TRY(d_sel.upload(sel, s));
   LSX_TRY(d_tiny.alloc(nm));
   LSX_TRY(d_flag.alloc(nm));
   LSX_TRY(d_Q.alloc(qsize));
+  LSX_TRY(d_rot.alloc(qsize / 1024));
   BJArgs g;
   g.A = A;
   g.VT = VT;
@@ -949,33 +955,27 @@ static lsx_status block_jacobi(hipStream_t s, const std::vector<int32_t>& sel, c
   g.ndim = d_ndim;
   g.tiny = d_tiny.p;
   g.Q = d_Q.p;
+  g.rotated = d_rot.p;
   g.flag = d_flag.p;
   LSX_HIP_TRY(launch_bj_init(s, (int)sel.size(), d_sel.p, g));
   std::vector<int32_t> flag(nm, 0);
   int sweep = 0;
   for (; sweep < maxsweeps && !act.empty(); ++sweep) {
     const int na = (int)act.size();
-    std::vector<int32_t> pp(na + 1, 0), pt(na + 1, 0);
-    for (int a = 0; a < na; ++a) {
-      const int np = ndim[act[a]] / 32;
-      pp[a + 1] = pp[a] + np;
-      pt[a + 1] = pt[a] + 2 * np * np;
-    }
+    std::vector<int32_t> pp(na + 1, 0);
+    for (int a = 0; a < na; ++a) pp[a + 1] = pp[a] + ndim[act[a]] / 32;
     LSX_TRY(d_mat.upload(act, s));
     LSX_TRY(d_pp.upload(pp, s));
-    LSX_TRY(d_pt.upload(pt, s));
     LSX_HIP_TRY(hipMemsetAsync(d_flag.p, 0, nm * sizeof(int32_t), s));
     g.mat = d_mat.p;
     g.pfx_pairs = d_pp.p;
-    g.pfx_tiles = d_pt.p;
     const int rounds = ndim[act[0]] / 16 - 1;
     int count = na;
     for (int r = 0; r < rounds; ++r) {
       // matrices with more than r + 1 blocks take part (a prefix: act is sorted by size)
       while (count > 0 && ndim[act[count - 1]] / 16 - 1 <= r) --count;
-      g.count = count;
       g.round = r;
-      LSX_HIP_TRY(launch_bj_round(s, pp[count], pt[count], g));
+      LSX_HIP_TRY(launch_bj_round(s, count, ndim[act[0]], g));
     }
     LSX_HIP_TRY(hipMemcpyAsync(flag.data(), d_flag.p, nm * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     LSX_HIP_TRY(hipStreamSynchronize(s));
@@ -1081,9 +1081,12 @@ static lsx_status precompute_layer(lsx_plan* pl, int layer, hipStream_t s) {
   std::vector<int64_t> moff(nu), loff(nu);
   int64_t mt = 0, lt = 0;
   int maxn = 0, maxL = 0;
-  // Matrices of more than kBlockedMin rows take the blocked solver (padded to a multiple of 32),
-  // the others the scalar one (padded to even); LSX_BLOCKED_JACOBI=0 keeps every fibre scalar.
-  const int blocked_min = env_int("LSX_BLOCKED_JACOBI", 1) != 0 ? kBlockedMin : 1 << 30;
+  // blocked or scalar solver (padded to even rows); LSX_BLOCKED_JACOBI=0 keeps every fibre scalar
+  int longest = 0;
+  for (int b = 0; b < nu; ++b) longest = std::max(longest, (embed + 1) * (ft.ptr[uniq[b] + 1] - ft.ptr[uniq[b]]));
+  const int blocked_min = env_int("LSX_BLOCKED_JACOBI", 1) == 0 ? 1 << 30
+                          : longest > kBlockedOnlyMin           ? kBlockedMin
+                                                                : kBlockedOnlyMin;
   std::vector<int32_t> sel_s, sel_b;
   int maxn_s = 0;
   for (int b = 0; b < nu; ++b) {
@@ -1128,7 +1131,7 @@ static lsx_status precompute_layer(lsx_plan* pl, int layer, hipStream_t s) {
   LSX_TRY(d_info.alloc(nu));
   // kinetic share of H_j: (1 - kappa)/nl * |K|^2/2
   const double kfac = (1.0 - pl->kappa) / sys->nl * 0.5;
-  LSX_HIP_TRY(launch_assemble(s, nu, d_fid.p, ld.ptr.p, ld.rows.p, d_mn.p, d, stride, own, kfac, pl->K2.p, S.nv,
+  LSX_HIP_TRY(launch_assemble(s, nu, maxn, d_fid.p, ld.ptr.p, ld.rows.p, d_mn.p, d, stride, own, kfac, pl->K2.p, S.nv,
                               d_vidx.p, d_vre.p, d_vim.p, embed, A.p, d_moff.p, d_ndim.p));
   std::vector<int32_t> info(nu, 0);
   if (!sel_s.empty()) {
@@ -1218,7 +1221,7 @@ static lsx_status precompute_layer(lsx_plan* pl, int layer, hipStream_t s) {
                             d_loff.p, ps.data.p, ps.off.p, dg));
     ps.present = true;
     if (banded && nband > 0) {
-      LSX_HIP_TRY(launch_band(s, pl->fmt, nu, d_fid.p, ld.ptr.p, ps.data.p, ps.off.p, d_boff.p, pl->band_tol,
+      LSX_HIP_TRY(launch_band(s, pl->fmt, nu, maxL, d_fid.p, ld.ptr.p, ps.data.p, ps.off.p, d_boff.p, pl->band_tol,
                               d_band.p));
       LSX_HIP_TRY(hipMemcpyAsync(hband.data(), d_band.p, hband.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
       LSX_HIP_TRY(hipStreamSynchronize(s));

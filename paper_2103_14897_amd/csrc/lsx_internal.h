@@ -128,16 +128,17 @@ struct PassArgs {
 };
 
 // ---------------------------------------------------------------- kernel launchers (lsx_kernels.hip)
-hipError_t launch_assemble(hipStream_t s, int nb, const int32_t* fid, const int32_t* ptr, const int32_t* rows,
+hipError_t launch_assemble(hipStream_t s, int nb, int maxn, const int32_t* fid, const int32_t* ptr, const int32_t* rows,
                            const int32_t* mn, int d, int stride, int own, double kfac, const double* K2, int nv,
                            const int32_t* vidx, const double* vre, const double* vim, int embed, double* A,
                            const int64_t* moff, const int32_t* ndim);
 // Blocked two-sided Jacobi (long fibres): arguments of one round.  Matrices are indexed by their
 // slot m (moff, ndim: padded size, a multiple of 32).  mat lists this sweep's unconverged
 // matrices by size, largest first; a round runs on the first `count` of them (those with more
-// than `round` + 1 blocks of 16).  pfx_pairs / pfx_tiles are prefix sums over mat of nb/2 pairs
-// and 2 (nb/2)^2 tiles (nb = n/16); Q holds every pair's 32x32 rotation (row-major) at its
-// pfx_pairs index; flag[m] is set to 1 when matrix m was rotated; tiny[m] is its skip threshold.
+// than `round` + 1 blocks of 16), maxn the largest.  pfx_pairs is the prefix sum over mat of nb/2
+// pairs (nb = n/16); Q holds every pair's 32x32 rotation (row-major) at its pfx_pairs index,
+// rotated[] whether it has any rotation; flag[m] is set to 1 when matrix m was rotated; tiny[m] is
+// its skip threshold.
 struct BJArgs {
   double* A = nullptr;
   double* VT = nullptr;
@@ -146,14 +147,13 @@ struct BJArgs {
   double* tiny = nullptr;
   const int32_t* mat = nullptr;
   const int32_t* pfx_pairs = nullptr;
-  const int32_t* pfx_tiles = nullptr;
-  int count = 0;
   int round = 0;
   double* Q = nullptr;
+  int32_t* rotated = nullptr;
   int32_t* flag = nullptr;
 };
 hipError_t launch_bj_init(hipStream_t s, int nsel, const int32_t* sel, const BJArgs& g);
-hipError_t launch_bj_round(hipStream_t s, int npairs, int ntiles, const BJArgs& g);
+hipError_t launch_bj_round(hipStream_t s, int count, int maxn, const BJArgs& g);
 hipError_t launch_bj_finish(hipStream_t s, int nsel, const int32_t* sel, const BJArgs& g, double* lam,
                             const int64_t* loff);
 
@@ -168,7 +168,7 @@ hipError_t launch_form(hipStream_t s, int fmt, int nb, int maxL, const int32_t* 
 // Band of every 16-row block of every stored propagator (k_band): band[2 (boff[b] + rb)] and
 // band[2 (boff[b] + rb) + 1] = first and one past the last column chunk with an entry whose
 // |Re| + |Im| >= tol (a block with none keeps its diagonal chunk).
-hipError_t launch_band(hipStream_t s, int fmt, int nb, const int32_t* fid, const int32_t* ptr, const void* P,
+hipError_t launch_band(hipStream_t s, int fmt, int nb, int maxL, const int32_t* fid, const int32_t* ptr, const void* P,
                        const int64_t* poff, const int64_t* boff, double tol, int32_t* band);
 hipError_t launch_phase_table(hipStream_t s, int64_t N, const double* K2, double theta_scale, double2* ph);
 hipError_t launch_phase_apply(hipStream_t s, int64_t N, int W, const double2* ph, double2* c);

@@ -28,7 +28,7 @@ __device__ double block_sum(double v, double* sh) {
 // embedding [[Re H, -Im H], [Im H, Re H]]; padding rows/cols are zero.  Row i's lifted
 // index is mn[i*stride ...]; layer j's own block starts at entry `own`; the kinetic share
 // on the diagonal is kfac |K|^2 with kfac = (1 - kappa) / (2 nl) for nl layers.
-// Block b assembles fibre fid[b] into its own slot b.
+// Workgroups (b, y) assemble fibre fid[b] into its own slot b.
 __global__ void k_assemble(const int32_t* fid, const int32_t* ptr, const int32_t* rows, const int32_t* mn, int d,
                            int stride, int own, double kfac, const double* K2, int nv, const int32_t* vidx,
                            const double* vre, const double* vim, int embed, double* Aall, const int64_t* moff,
@@ -40,7 +40,7 @@ __global__ void k_assemble(const int32_t* fid, const int32_t* ptr, const int32_t
   double* A = Aall + moff[b];
   const int La = embed ? 2 * L : L;
   const int64_t nn = (int64_t)n * n;
-  for (int64_t e = threadIdx.x; e < nn; e += blockDim.x) {
+  for (int64_t e = blockIdx.y * blockDim.x + threadIdx.x; e < nn; e += gridDim.y * blockDim.x) {
     const int a = (int)(e / n), b = (int)(e % n);
     double val = 0.0;
     if (a < La && b < La) {
@@ -193,24 +193,13 @@ __global__ __launch_bounds__(BS) void k_jacobi(double* Aall, double* VTall, cons
 // For long fibres.  A matrix of padded size n (a multiple of 32; padding rows and columns are
 // zero and are never rotated) is cut into nb = n/16 blocks of 16 rows.  A round pairs the
 // blocks with the same circle method the scalar solver uses for rows, into nb/2 disjoint pairs
-// P = (I, J).  For every pair the 32x32 diagonal subproblem A[P, P] takes one cyclic Jacobi
-// sweep in LDS, whose rotations accumulate into Q_P; then every 32x32 tile of A and of V^T is
+// P = (I, J).  For every pair the 32x32 diagonal subproblem A[P, P] is rotated in LDS (its share
+// of one cyclic Jacobi sweep), the rotations accumulating into Q_P; then every 32x32 tile of A and of V^T is
 // replaced, A[P, P'] <- Q_P^T A[P, P'] Q_P' and V^T[P, R] <- Q_P^T V^T[P, R] (R: 32 columns).
 // Each output tile depends only on its own input tile and two rotations, so a round is two
 // launches with no other synchronisation, and the tile products run on the FP64 matrix cores.
 // A sweep with no rotation in any subproblem leaves every off-diagonal entry below the same
-// threshold as the scalar solver's; the same rotation formula and final normalisation apply.
-
-// slot a of a prefix-sum table with pfx[a] <= item < pfx[a + 1] (pfx[0] = 0, item < pfx[count])
-__device__ __forceinline__ int bj_slot(const int32_t* pfx, int count, int item) {
-  int lo = 0, hi = count;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (pfx[mid] <= item) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
+// threshold as the scalar solver's; the same final normalisation applies.
 
 // blocks (I, J) of pair i in round r of nb blocks (circle method, nb even)
 __device__ __forceinline__ void bj_pair(int nb, int r, int i, int& I, int& J) {
@@ -240,109 +229,134 @@ __global__ __launch_bounds__(1024) void k_bj_init(BJArgs g, const int32_t* sel) 
   if (threadIdx.x == 0) g.tiny[m] = 1e-16 * normF;
 }
 
+// 1 / sqrt(x) for x in [0.25, 8): the hardware estimate with one third-order and one second-order
+// correction.
+__device__ __forceinline__ double rsqrt_f64(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  double e = fma(-x * y, y, 1.0);
+  y = fma(y * e, fma(0.375, e, 0.5), y);
+  e = fma(-x * y, y, 1.0);
+  return fma(0.5 * y, e, y);
+}
+
+// Rotation (c, s) of the pair with entries app, aqq, apq; false: apq is below the threshold and stays.
+// The scalar solver's angle, tan = sgn(d / apq) 2 |apq| / (|d| + h) with d = aqq - app and
+// h = sqrt(d^2 + 4 apq^2), from two reciprocal roots: c^2 = (1 + |d| / h) / 2, |s| = |apq| / (h c).
+// d and apq are scaled by a power of two first, so that no square leaves the range.
+__device__ __forceinline__ bool bj_rotation(double app, double aqq, double apq, double tiny, double& c, double& s) {
+  c = 1.0;
+  s = 0.0;
+  const double over = fabs(apq) - tiny;  // rotated when |apq| > tiny + 1e-16 sqrt|app aqq|
+  if (!(over > 0.0 && over * over > 1e-32 * fabs(app * aqq))) return false;
+  double d = aqq - app;
+  const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(apq)));
+  d = __builtin_amdgcn_ldexp(d, -e);
+  const double a = __builtin_amdgcn_ldexp(apq, -e);
+  const double r = rsqrt_f64(fma(d, d, 4.0 * a * a));
+  const double x = fma(0.5 * fabs(d), r, 0.5);
+  const double y = rsqrt_f64(x);
+  c = x * y;
+  s = (d >= 0.0 ? a : -a) * r * y;
+  return true;
+}
+
+// Every index pair of the matrix meets once a sweep: the pairs across the two blocks of P in sixteen
+// rounds here, the pairs inside a block in the fifteen before them in the sweep's first round of
+// blocks.  A round takes one barrier: every wave works out all sixteen rotations and S alternates between two arrays.  Bound by the latency of that chain (LDS, two
+// reciprocal roots, lane exchange, LDS), and by its fixed part (launch, loads) in the rounds
+// that rotate nothing: 13.6 us a launch on average (twisted bilayer, N = 82321, 459 launches), 25.7
+// (432 launches) with every pair in every block round, three divisions and three roots a rotation
+// and two barriers.
 __global__ __launch_bounds__(256) void k_bj_pairs(BJArgs g) {
-  __shared__ double S[32][33];
+  __shared__ double S[2][32][33];
   __shared__ double Qs[32][33];
-  __shared__ double rc[16], rs[16];
-  __shared__ int rp[16], rq[16];
-  __shared__ int rot;
-  const int item = blockIdx.x;
-  const int a = bj_slot(g.pfx_pairs, g.count, item);
+  const int i = blockIdx.x, a = blockIdx.y;
   const int m = g.mat[a];
-  const int i = item - g.pfx_pairs[a];
   const int n = g.ndim[m];
+  if (i >= n >> 5) return;
   int I, J;
   bj_pair(n >> 4, g.round, i, I, J);
   const double* A = g.A + g.moff[m];
   const int tid = threadIdx.x;
-  if (tid == 0) rot = 0;
   for (int e = tid; e < 1024; e += 256) {
     const int x = e >> 5, y = e & 31;
     const int gx = (x < 16 ? I : J) * 16 + (x & 15), gy = (y < 16 ? I : J) * 16 + (y & 15);
-    S[x][y] = A[(int64_t)gx * n + gy];
+    S[0][x][y] = A[(int64_t)gx * n + gy];
     Qs[x][y] = (x == y) ? 1.0 : 0.0;
   }
   const double tiny = g.tiny[m];
-  __syncthreads();
-  for (int r = 0; r < 31; ++r) {
-    if (tid < 16) {
-      const int p = (tid == 0) ? 31 : (r + tid) % 31;
-      const int q = (tid == 0) ? r : (r - tid + 31) % 31;
-      const double app = S[p][p], aqq = S[q][q], apq = S[p][q];
-      double c = 1.0, sn = 0.0;
-      if (fabs(apq) > 1e-16 * sqrt(fabs(app * aqq)) + tiny) {
-        const double th = (aqq - app) / (2.0 * apq);
-        const double t = (fabs(th) > 1e150) ? 0.5 / th
-                                            : ((th >= 0.0) ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-        c = 1.0 / sqrt(t * t + 1.0);
-        sn = t * c;
-        rot = 1;
-      }
-      rc[tid] = c;
-      rs[tid] = sn;
-      rp[tid] = p;
-      rq[tid] = q;
-    }
-    __syncthreads();
-    {
-      // S <- J^T S J one 2x2 block per thread: rows (p_bi, q_bi), columns (p_bj, q_bj)
-      const int bi = tid >> 4, bj = tid & 15;
-      const double ci = rc[bi], si = rs[bi], cj = rc[bj], sj = rs[bj];
-      if (si != 0.0 || sj != 0.0) {
-        const int p = rp[bi], q = rq[bi], p2 = rp[bj], q2 = rq[bj];
-        const double a0 = S[p][p2], b0 = S[p][q2], c0 = S[q][p2], d0 = S[q][q2];
-        const double a1 = ci * a0 - si * c0, b1 = ci * b0 - si * d0;
-        const double c1 = si * a0 + ci * c0, d1 = si * b0 + ci * d0;
-        double a2 = cj * a1 - sj * b1, b2 = sj * a1 + cj * b1;
-        double c2 = cj * c1 - sj * d1, d2 = sj * c1 + cj * d1;
-        if (bi == bj) {
-          b2 = 0.0;
-          c2 = 0.0;
-        }
-        S[p][p2] = a2;
-        S[p][q2] = b2;
-        S[q][p2] = c2;
-        S[q][q2] = d2;
-      }
-      // Q <- Q J: columns (p_k, q_k) of rows x and x + 16
-      const int k = tid & 15, x0 = tid >> 4;
-      const double c = rc[k], sn = rs[k];
-      if (sn != 0.0) {
-        const int p = rp[k], q = rq[k];
+  const int bi = tid >> 4, bj = tid & 15;
+  int cur = 0;
+  bool any = false;
+  // S <- J^T S J, rows (p, q), columns (p2, q2) by this thread; Q <- Q J, columns (p2, q2) of rows bi
+  // and bi + 16
+  auto round = [&](int p, int q, int p2, int q2) {
+    const double(*X)[33] = S[cur];
+    double(*Y)[33] = S[cur ^ 1];
+    double cj, sj;
+    const bool rj = bj_rotation(X[p2][p2], X[q2][q2], X[p2][q2], tiny, cj, sj);
+    any |= rj;
+    const double ci = __shfl(cj, bi), si = __shfl(sj, bi);  // lane bi of each wave has pair bi's
+    const double a0 = X[p][p2], b0 = X[p][q2], c0 = X[q][p2], d0 = X[q][q2];
+    const double a1 = ci * a0 - si * c0, b1 = ci * b0 - si * d0;
+    const double c1 = si * a0 + ci * c0, d1 = si * b0 + ci * d0;
+    const bool own = bi == bj && rj;  // the rotated pair's own entry
+    Y[p][p2] = cj * a1 - sj * b1;
+    Y[p][q2] = own ? 0.0 : sj * a1 + cj * b1;
+    Y[q][p2] = own ? 0.0 : cj * c1 - sj * d1;
+    Y[q][q2] = sj * c1 + cj * d1;
+    if (rj) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int x = x0 + 16 * h;
-          const double u = Qs[x][p], v = Qs[x][q];
-          Qs[x][p] = c * u - sn * v;
-          Qs[x][q] = sn * u + c * v;
-        }
+      for (int h = 0; h < 2; ++h) {
+        const double u = Qs[bi + 16 * h][p2], v = Qs[bi + 16 * h][q2];
+        Qs[bi + 16 * h][p2] = cj * u - sj * v;
+        Qs[bi + 16 * h][q2] = sj * u + cj * v;
       }
     }
+    cur ^= 1;
     __syncthreads();
+  };
+  __syncthreads();
+  if (g.round == 0) {
+    // circle method inside each block: pair k < 8 in the first, k >= 8 in the second
+#pragma unroll 1
+    for (int r = 0; r < 15; ++r) {
+      auto first = [&](int k) { return (k & 7) == 0 ? 15 : (r + (k & 7)) % 15; };
+      auto second = [&](int k) { return (k & 7) == 0 ? r : (r - (k & 7) + 15) % 15; };
+      const int oi = (bi & 8) * 2, oj = (bj & 8) * 2;
+      round(oi + first(bi), oi + second(bi), oj + first(bj), oj + second(bj));
+    }
   }
-  double* Qo = g.Q + ((int64_t)g.pfx_pairs[a] + i) * 1024;
+#pragma unroll 4
+  for (int r = 0; r < 16; ++r) round(bi, 16 + ((bi + r) & 15), bj, 16 + ((bj + r) & 15));
+  const int item = g.pfx_pairs[a] + i;
+  double* Qo = g.Q + (int64_t)item * 1024;
   for (int e = tid; e < 1024; e += 256) Qo[e] = Qs[e >> 5][e & 31];
-  if (tid == 0 && rot) g.flag[m] = 1;
+  const int rot = __syncthreads_or(any);
+  if (tid == 0) {
+    g.rotated[item] = rot;
+    if (rot) g.flag[m] = 1;
+  }
 }
 
 // One wave per 32x32 tile, four tiles per workgroup.  v_mfma_f64_16x16x4f64 takes A as lane l =
 // A[l % 16][l / 16] and B as B[l / 16][l % 16] of a 16x4 / 4x16 step and leaves C[4 r + l / 16]
 // [l % 16] in element r, so the accumulators of X = A_t Q_P' are, element for element, the B
 // operands of the second product Q_P^T X.
-__global__ LSX_MFMA_BOUNDS(256, true) void k_bj_tiles(BJArgs g, int total) {
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int item = blockIdx.x * 4 + wv;
-  if (item >= total) return;
-  const int a = bj_slot(g.pfx_tiles, g.count, item);
+__global__ LSX_MFMA_BOUNDS(256, true) void k_bj_tiles(BJArgs g) {
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int t = blockIdx.x * 4 + wv, a = blockIdx.y;
   const int m = g.mat[a];
-  const int t = item - g.pfx_tiles[a];
   const int n = g.ndim[m], nb = n >> 4, np = nb >> 1;
+  if (t >= 2 * np * np) return;
   const int li = lane & 15, lk = lane >> 4;
   const double* Qb = g.Q + (int64_t)g.pfx_pairs[a] * 1024;
   const v4d zero4 = {0.0, 0.0, 0.0, 0.0};
   v4d T[2][2] = {{zero4, zero4}, {zero4, zero4}};
+  const int32_t* rotated = g.rotated + g.pfx_pairs[a];  // tiles between unrotated pairs stay as they are
   if (t < np * np) {
     const int P = t / np, P2 = t - (t / np) * np;
+    if (!rotated[P] && !rotated[P2]) return;
     int I, J, I2, J2;
     bj_pair(nb, g.round, P, I, J);
     bj_pair(nb, g.round, P2, I2, J2);
@@ -382,6 +396,7 @@ __global__ LSX_MFMA_BOUNDS(256, true) void k_bj_tiles(BJArgs g, int total) {
   } else {
     const int tv = t - np * np;
     const int P = tv / np, R = tv - (tv / np) * np;
+    if (!rotated[P]) return;
     int I, J;
     bj_pair(nb, g.round, P, I, J);
     double* VT = g.VT + g.moff[m];
@@ -419,12 +434,13 @@ hipError_t launch_bj_init(hipStream_t s, int nsel, const int32_t* sel, const BJA
   return hipGetLastError();
 }
 
-hipError_t launch_bj_round(hipStream_t s, int npairs, int ntiles, const BJArgs& g) {
-  if (npairs == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_bj_pairs, dim3(npairs), dim3(256), 0, s, g);
+hipError_t launch_bj_round(hipStream_t s, int count, int maxn, const BJArgs& g) {
+  if (count == 0) return hipSuccess;
+  const int np = maxn / 32;
+  hipLaunchKernelGGL(k_bj_pairs, dim3(np, count), dim3(256), 0, s, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_bj_tiles, dim3((ntiles + 3) / 4), dim3(256), 0, s, g, ntiles);
+  hipLaunchKernelGGL(k_bj_tiles, dim3((2 * np * np + 3) / 4, count), dim3(256), 0, s, g);
   return hipGetLastError();
 }
 
@@ -466,57 +482,113 @@ __global__ void k_eig_fn(int64_t nlam, const double* lam, double t, int flow, do
 // P(t) = f(H) = sum_k V[.][k] f(lambda_k) V[.][k]^T with f = g + i h.  For an embedded
 // complex H (real form M = [[Re H, -Im H], [Im H, Re H]]), g(M) and h(M) hold Re/Im of g(H)
 // and h(H) in their left blocks (C_A, C_B and S_A, S_B), so P = (C_A - S_B) + i (C_B + S_A).
-// Block b forms fibre fid[b] (slot b); the mixed formats' diagonal goes to positions ptr[f]+a.
+// Workgroups (b, y) form fibre fid[b] (slot b); the mixed formats' diagonal goes to positions ptr[f]+a.
+//
+// A contraction over the eigenvectors, on the FP64 matrix cores: a wave takes a 16-row block by 16
+// NB columns, with the entries' columns as the matrix rows and the entries' rows as the matrix columns,
+// so that C[4 r + l / 16][l % 16] of lane l is element l of chunk 4 cb + r of the stored order and both
+// operands are rows of V^T as they lie.  Twisted bilayer, N = 82321: 187 us a propagator set, 1.9 ms
+// with one entry a thread and no operand shared.
+template <int FMT, bool EMB>
+__device__ __forceinline__ void form_tile(const double* VT, const double2* gh, int n, int L, int rb, int cb0, char* P,
+                                          double2* diag) {
+  constexpr int NB = 2;
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const v4d zero4 = {0.0, 0.0, 0.0, 0.0};
+  v4d CA[NB], SA[NB], CB[NB], SB[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) CA[nb] = SA[nb] = CB[nb] = SB[nb] = zero4;
+  const int arow = 16 * rb + li;
+  const bool rok = arow < L;
+  int col[NB];
+  bool cok[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    col[nb] = 16 * (cb0 + nb) + li;
+    cok[nb] = col[nb] < L;
+  }
+  constexpr int U = 4;
+  struct Step {
+    double u, u2, v[NB];
+    double2 c;
+  };
+  // k-step ks: eigenvectors 4 ks + lk; entries outside the fibre are zero
+  auto load = [&](Step& s, int ks) {
+    const int k = 4 * ks + lk;
+    const bool ok = k < n;
+    const double* row = VT + (int64_t)(ok ? k : 0) * n;
+    s.u = ok && rok ? row[arow] : 0.0;
+    if (EMB) s.u2 = ok && rok ? row[L + arow] : 0.0;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) s.v[nb] = ok && cok[nb] ? row[col[nb]] : 0.0;
+    s.c = ok ? gh[k] : make_double2(0.0, 0.0);
+  };
+  const int nks = (n + 3) >> 2;
+  Step A[U];
+#pragma unroll
+  for (int j = 0; j < U; ++j) load(A[j], j);
+  for (int ks = 0; ks < nks; ks += U) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const Step s = A[j];
+      load(A[j], ks + U + j);
+      const double uc = s.u * s.c.x, us = s.u * s.c.y;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        CA[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(s.v[nb], uc, CA[nb], 0, 0, 0);
+        SA[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(s.v[nb], us, SA[nb], 0, 0, 0);
+        if (EMB) {
+          CB[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(s.v[nb], s.u2 * s.c.x, CB[nb], 0, 0, 0);
+          SB[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(s.v[nb], s.u2 * s.c.y, SB[nb], 0, 0, 0);
+        }
+      }
+    }
+  }
+  if (!rok) return;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int bb = 16 * (cb0 + nb) + 4 * r + lk;
+      if (bb >= L) continue;
+      const double pr = EMB ? CA[nb][r] - SB[nb][r] : CA[nb][r], pi = EMB ? CB[nb][r] + SA[nb][r] : SA[nb][r];
+      if (FMT != PF_F64 && arow == bb) {
+        diag[arow] = make_double2(pr, pi);
+      } else if (FMT == PF_BF16X3) {
+        const int Lp = (L + 31) & ~31;
+        const int64_t chunk = (int64_t)rb * (Lp >> 5) + (bb >> 5);
+        const int el = bb & 7;
+        unsigned short* Q = reinterpret_cast<unsigned short*>(P);
+        unsigned short t[6];
+        split3(pr, t[0], t[2], t[4]);
+        split3(pi, t[1], t[3], t[5]);
+#pragma unroll
+        for (int pl = 0; pl < 6; ++pl) Q[((chunk * 6 + pl) * 64 + li + 16 * ((bb & 31) >> 3)) * 8 + el] = t[pl];
+      } else {
+        const int Lp = (L + 15) & ~15;
+        const int64_t idx = ((int64_t)rb * (Lp >> 2) + (bb >> 2)) * 64 + lane;
+        if (FMT == PF_F64) reinterpret_cast<double2*>(P)[idx] = make_double2(pr, pi);
+        else reinterpret_cast<float2*>(P)[idx] = make_float2((float)pr, (float)pi);
+      }
+    }
+}
+
 template <int FMT>
-__global__ void k_form(const int32_t* fid, const int32_t* ptr, const double* VTall, const int64_t* moff,
-                       const int32_t* ndim, const int32_t* embed, const double2* ghall, const int64_t* loff,
-                       void* Pall, const int64_t* poff, double2* diag) {
+__global__ LSX_MFMA_BOUNDS(256, true) void k_form(const int32_t* fid, const int32_t* ptr, const double* VTall,
+                                                  const int64_t* moff, const int32_t* ndim, const int32_t* embed,
+                                                  const double2* ghall, const int64_t* loff, void* Pall,
+                                                  const int64_t* poff, double2* diag) {
   const int b = blockIdx.x;
   const int f = fid[b];
   const int r0 = ptr[f], L = ptr[f + 1] - r0;
-  const int n = ndim[b];
-  const int emb = embed[b];
   const double* VT = VTall + moff[b];
   const double2* gh = ghall + loff[b];
   char* P = reinterpret_cast<char*>(Pall) + poff[b];
-  const int LL = L * L;
-  for (int e = blockIdx.y * blockDim.x + threadIdx.x; e < LL; e += gridDim.y * blockDim.x) {
-    const int a = e / L, bb = e - (e / L) * L;
-    double CA = 0.0, SA = 0.0, CB = 0.0, SB = 0.0;
-    for (int k = 0; k < n; ++k) {
-      const double2 c = gh[k];
-      const double v = VT[(int64_t)k * n + bb];
-      const double uv = VT[(int64_t)k * n + a] * v;
-      CA += uv * c.x;
-      SA += uv * c.y;
-      if (emb) {
-        const double u2v = VT[(int64_t)k * n + L + a] * v;
-        CB += u2v * c.x;
-        SB += u2v * c.y;
-      }
-    }
-    const double pr = CA - SB, pi = CB + SA;
-    if (FMT == PF_F64) {
-      const int Lp = (L + 15) & ~15;
-      const int64_t idx = ((int64_t)(a >> 4) * (Lp >> 2) + (bb >> 2)) * 64 + (a & 15) + 16 * (bb & 3);
-      reinterpret_cast<double2*>(P)[idx] = make_double2(pr, pi);
-    } else if (a == bb) {
-      diag[r0 + a] = make_double2(pr, pi);
-    } else if (FMT == PF_F32) {
-      const int Lp = (L + 15) & ~15;
-      const int64_t idx = ((int64_t)(a >> 4) * (Lp >> 2) + (bb >> 2)) * 64 + (a & 15) + 16 * (bb & 3);
-      reinterpret_cast<float2*>(P)[idx] = make_float2((float)pr, (float)pi);
-    } else {
-      const int Lp = (L + 31) & ~31;
-      const int64_t chunk = (int64_t)(a >> 4) * (Lp >> 5) + (bb >> 5);
-      const int lane = (a & 15) + 16 * ((bb & 31) >> 3), el = bb & 7;
-      unsigned short* Q = reinterpret_cast<unsigned short*>(P);
-      unsigned short t[6];
-      split3(pr, t[0], t[2], t[4]);
-      split3(pi, t[1], t[3], t[5]);
-#pragma unroll
-      for (int pl = 0; pl < 6; ++pl) Q[((chunk * 6 + pl) * 64 + lane) * 8 + el] = t[pl];
-    }
+  const int nrb = (L + 15) >> 4, ncb = (L + 31) >> 5;
+  for (int u = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); u < nrb * ncb; u += 4 * gridDim.y) {
+    const int rb = u / ncb, cb0 = 2 * (u - rb * ncb);
+    if (embed[b]) form_tile<FMT, true>(VT, gh, ndim[b], L, rb, cb0, P, diag + (FMT == PF_F64 ? 0 : r0));
+    else form_tile<FMT, false>(VT, gh, ndim[b], L, rb, cb0, P, diag + (FMT == PF_F64 ? 0 : r0));
   }
 }
 
@@ -527,13 +599,14 @@ __global__ void k_form(const int32_t* fid, const int32_t* ptr, const double* VTa
 // a product could feel.  For every 16-row block of every stored propagator this records the
 // first and one past the last column chunk (4 columns; 32 for the BF16x3 format) that holds an
 // entry with |Re| + |Im| >= tol (for BF16x3 the sum over the three terms' magnitudes bounds
-// the entry); a block with no such entry keeps its diagonal chunk.  One workgroup per stored
-// propagator; wave w takes row blocks w, w + 4, ...
+// the entry); a block with no such entry keeps its diagonal chunk.  Workgroups (b, y) take stored
+// propagator b, one row block a wave.
 template <int FMT>
 __global__ __launch_bounds__(256) void k_band(const int32_t* fid, const int32_t* ptr, const void* Pall,
                                               const int64_t* poff, const int64_t* boff, double tol,
                                               int32_t* band) {
   constexpr int CW = FMT == PF_BF16X3 ? 32 : 4;
+  constexpr int G = FMT == PF_BF16X3 ? 1 : 8;  // chunks read together
   const int b = blockIdx.x;
   const int f = fid[b];
   const int L = ptr[f + 1] - ptr[f];
@@ -541,34 +614,40 @@ __global__ __launch_bounds__(256) void k_band(const int32_t* fid, const int32_t*
   const int nc = Lp / CW, nrb = (L + 15) >> 4;
   const int lane = threadIdx.x & 63;
   const char* P = reinterpret_cast<const char*>(Pall) + poff[b];
-  for (int rb = threadIdx.x >> 6; rb < nrb; rb += blockDim.x >> 6) {
+  for (int rb = 4 * blockIdx.y + (threadIdx.x >> 6); rb < nrb; rb += 4 * gridDim.y) {
     int lo = -1, hi = -1;
-    for (int kc = 0; kc < nc; ++kc) {
-      const int64_t ch = (int64_t)rb * nc + kc;
-      bool big = false;
-      if (FMT == PF_F64) {
-        const double2 v = reinterpret_cast<const double2*>(P)[ch * 64 + lane];
-        big = fabs(v.x) + fabs(v.y) >= tol;
-      } else if (FMT == PF_F32) {
-        const float2 v = reinterpret_cast<const float2*>(P)[ch * 64 + lane];
-        big = (double)fabsf(v.x) + (double)fabsf(v.y) >= tol;
-      } else {
-        const v8u16* Q = reinterpret_cast<const v8u16*>(P) + ch * 6 * 64 + lane;
-        v8u16 pl[6];
+    for (int kc0 = 0; kc0 < nc; kc0 += G) {
+      bool big[G];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) pl[k] = Q[k * 64];
+      for (int j = 0; j < G; ++j) {
+        const int64_t ch = (int64_t)rb * nc + min(kc0 + j, nc - 1);
+        if (FMT == PF_F64) {
+          const double2 v = reinterpret_cast<const double2*>(P)[ch * 64 + lane];
+          big[j] = fabs(v.x) + fabs(v.y) >= tol;
+        } else if (FMT == PF_F32) {
+          const float2 v = reinterpret_cast<const float2*>(P)[ch * 64 + lane];
+          big[j] = (double)fabsf(v.x) + (double)fabsf(v.y) >= tol;
+        } else {
+          const v8u16* Q = reinterpret_cast<const v8u16*>(P) + ch * 6 * 64 + lane;
+          v8u16 pl[6];
 #pragma unroll
-        for (int el = 0; el < 8; ++el) {
-          double m = 0.0;
+          for (int k = 0; k < 6; ++k) pl[k] = Q[k * 64];
+          big[j] = false;
 #pragma unroll
-          for (int k = 0; k < 6; ++k) m += fabs((double)bf2f(pl[k][el]));
-          big = big || m >= tol;
+          for (int el = 0; el < 8; ++el) {
+            double m = 0.0;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) m += fabs((double)bf2f(pl[k][el]));
+            big[j] = big[j] || m >= tol;
+          }
         }
       }
-      if (__any(big)) {
-        if (lo < 0) lo = kc;
-        hi = kc + 1;
-      }
+#pragma unroll
+      for (int j = 0; j < G; ++j)
+        if (__any(big[j]) && kc0 + j < nc) {
+          if (lo < 0) lo = kc0 + j;
+          hi = kc0 + j + 1;
+        }
     }
     if (lo < 0) {
       lo = (16 * rb) / CW;
@@ -582,11 +661,12 @@ __global__ __launch_bounds__(256) void k_band(const int32_t* fid, const int32_t*
 }
 
 // ================================================================ launchers
-hipError_t launch_assemble(hipStream_t s, int nb, const int32_t* fid, const int32_t* ptr, const int32_t* rows,
+hipError_t launch_assemble(hipStream_t s, int nb, int maxn, const int32_t* fid, const int32_t* ptr, const int32_t* rows,
                            const int32_t* mn, int d, int stride, int own, double kfac, const double* K2, int nv,
                            const int32_t* vidx, const double* vre, const double* vim, int embed, double* A,
                            const int64_t* moff, const int32_t* ndim) {
-  hipLaunchKernelGGL(k_assemble, dim3(nb), dim3(256), 0, s, fid, ptr, rows, mn, d, stride, own, kfac, K2, nv, vidx,
+  const unsigned gy = (unsigned)std::max<int64_t>(1, std::min<int64_t>(((int64_t)maxn * maxn + 1023) / 1024, 256));
+  hipLaunchKernelGGL(k_assemble, dim3(nb, gy), dim3(256), 0, s, fid, ptr, rows, mn, d, stride, own, kfac, K2, nv, vidx,
                      vre, vim, embed, A, moff, ndim);
   return hipGetLastError();
 }
@@ -611,23 +691,24 @@ hipError_t launch_eig_fn(hipStream_t s, int64_t nlam, const double* lam, double 
   return hipGetLastError();
 }
 
-hipError_t launch_band(hipStream_t s, int fmt, int nb, const int32_t* fid, const int32_t* ptr, const void* P,
+hipError_t launch_band(hipStream_t s, int fmt, int nb, int maxL, const int32_t* fid, const int32_t* ptr, const void* P,
                        const int64_t* poff, const int64_t* boff, double tol, int32_t* band) {
   if (nb == 0) return hipSuccess;
+  const dim3 g(nb, (unsigned)std::min(64, std::max(1, (maxL + 63) / 64)));
   if (fmt == PF_F64)
-    hipLaunchKernelGGL(k_band<PF_F64>, dim3(nb), dim3(256), 0, s, fid, ptr, P, poff, boff, tol, band);
+    hipLaunchKernelGGL(k_band<PF_F64>, g, dim3(256), 0, s, fid, ptr, P, poff, boff, tol, band);
   else if (fmt == PF_F32)
-    hipLaunchKernelGGL(k_band<PF_F32>, dim3(nb), dim3(256), 0, s, fid, ptr, P, poff, boff, tol, band);
+    hipLaunchKernelGGL(k_band<PF_F32>, g, dim3(256), 0, s, fid, ptr, P, poff, boff, tol, band);
   else
-    hipLaunchKernelGGL(k_band<PF_BF16X3>, dim3(nb), dim3(256), 0, s, fid, ptr, P, poff, boff, tol, band);
+    hipLaunchKernelGGL(k_band<PF_BF16X3>, g, dim3(256), 0, s, fid, ptr, P, poff, boff, tol, band);
   return hipGetLastError();
 }
 
 hipError_t launch_form(hipStream_t s, int fmt, int nb, int maxL, const int32_t* fid, const int32_t* ptr,
                        const double* VT, const int64_t* moff, const int32_t* ndim, const int32_t* embed,
                        const double2* gh, const int64_t* loff, void* P, const int64_t* poff, double2* diag) {
-  const int64_t maxLL = (int64_t)maxL * maxL;
-  const unsigned gy = (unsigned)std::max<int64_t>(1, std::min<int64_t>((maxLL + 255) / 256, 4096));
+  const int64_t units = (int64_t)((maxL + 15) / 16) * ((maxL + 31) / 32);
+  const unsigned gy = (unsigned)std::max<int64_t>(1, std::min<int64_t>((units + 3) / 4, 4096));
   const dim3 g(nb, gy);
   if (fmt == PF_F64)
     hipLaunchKernelGGL(k_form<PF_F64>, g, dim3(256), 0, s, fid, ptr, VT, moff, ndim, embed, gh, loff, P, poff, diag);
