@@ -767,7 +767,37 @@ struct PointSym {
   int32_t M[kMaxLayers][4];  // d x d integer matrix per layer, row-major
 };
 
-static std::vector<PointSym> find_point_symmetries(const lsx_system* sys) {
+// Canonical row of every lifted index: open addressing with linear probing on the packed index, at
+// most half full.
+struct IndexTable {
+  std::vector<uint64_t> key;
+  std::vector<int32_t> row;
+  uint64_t mask = 0;
+  void build(const lsx_system* sys) {
+    uint64_t n = 16;
+    while (n < 2 * (uint64_t)sys->N) n *= 2;
+    mask = n - 1;
+    key.assign(n, 0);
+    row.assign(n, -1);
+    for (int64_t i = 0; i < sys->N; ++i) {
+      const uint64_t k = pack_key(&sys->mn[i * sys->S], sys->S);
+      uint64_t h = slot(k);
+      while (row[h] >= 0) h = (h + 1) & mask;
+      key[h] = k;
+      row[h] = (int32_t)i;
+    }
+  }
+  uint64_t slot(uint64_t k) const { return (k * 0x9E3779B97F4A7C15ull >> 20) & mask; }
+  int32_t find(uint64_t k) const {  // -1: not in the set
+    uint64_t h = slot(k);
+    while (row[h] >= 0 && key[h] != k) h = (h + 1) & mask;
+    return row[h];
+  }
+};
+
+// images (nullable): per symmetry, the canonical row every canonical row maps to
+static std::vector<PointSym> find_point_symmetries(const lsx_system* sys,
+                                                   std::vector<std::vector<int32_t>>* images = nullptr) {
   std::vector<PointSym> out;
   if (!sys->standard || sys->N == 0) return out;
   const int d = sys->d, nl = sys->nl;
@@ -780,9 +810,14 @@ static std::vector<PointSym> find_point_symmetries(const lsx_system* sys) {
       Rs.push_back({std::cos(th), -std::sin(th), std::sin(th), std::cos(th)});
     }
   }
-  std::unordered_map<uint64_t, int32_t> where;
+  IndexTable where;
   const int S = sys->S;
-  for (const auto& R : Rs) {
+  // The rotations are by k angles of one step, k = 1, 2, ...; where k0 is the first symmetry and
+  // k - k0 is one, the images under k are those under k0 of those under k - k0.
+  std::vector<std::vector<int32_t>> to(Rs.size());  // empty: not a symmetry
+  size_t k0 = Rs.size();
+  for (size_t k = 0; k < Rs.size(); ++k) {
+    const std::vector<double>& R = Rs[k];
     PointSym g{};
     bool ok = true;
     for (int j = 0; j < nl && ok; ++j) {
@@ -830,22 +865,34 @@ static std::vector<PointSym> find_point_symmetries(const lsx_system* sys) {
     }
     if (!ok) continue;
     // the lifted index set maps onto itself
-    if (where.empty())
-      for (int64_t i = 0; i < sys->N; ++i) where[pack_key(&sys->mn[i * S], S)] = (int32_t)i;
-    int32_t img[kMaxIndex];
-    for (int64_t i = 0; i < sys->N && ok; ++i) {
-      const int32_t* m = &sys->mn[i * S];
-      for (int j = 0; j < nl; ++j)
-        for (int r = 0; r < d; ++r) {
-          int64_t acc = 0;
-          for (int c = 0; c < d; ++c) acc += (int64_t)g.M[j][r * d + c] * m[j * d + c];
-          if (std::llabs(acc) > (S <= 4 ? 32767 : 511)) ok = false;
-          img[j * d + r] = (int32_t)acc;
-        }
-      ok = ok && where.count(pack_key(img, S)) > 0;
+    to[k].resize((size_t)sys->N);
+    if (k0 < k && !to[k - k0 - 1].empty()) {
+      for (int64_t i = 0; i < sys->N; ++i) to[k][i] = to[k0][to[k - k0 - 1][i]];
+    } else {
+      if (where.row.empty()) where.build(sys);
+      int32_t img[kMaxIndex];
+      for (int64_t i = 0; i < sys->N && ok; ++i) {
+        const int32_t* m = &sys->mn[i * S];
+        for (int j = 0; j < nl; ++j)
+          for (int r = 0; r < d; ++r) {
+            int64_t acc = 0;
+            for (int c = 0; c < d; ++c) acc += (int64_t)g.M[j][r * d + c] * m[j * d + c];
+            if (std::llabs(acc) > (S <= 4 ? 32767 : 511)) ok = false;
+            img[j * d + r] = (int32_t)acc;
+          }
+        ok = ok && (to[k][i] = where.find(pack_key(img, S))) >= 0;
+      }
     }
-    if (ok) out.push_back(g);
+    if (!ok) {
+      to[k].clear();
+      continue;
+    }
+    out.push_back(g);
+    if (k0 == Rs.size()) k0 = k;
   }
+  if (images)
+    for (std::vector<int32_t>& t : to)
+      if (!t.empty()) images->push_back(std::move(t));
   return out;
 }
 
@@ -865,13 +912,10 @@ extern "C" lsx_status lsx_system_symmetries(const lsx_system* sys, int32_t* nsym
 // The plan's row order of every layer and, with point symmetries, each fibre's representative.
 static void plan_orders(lsx_plan* pl, bool use_sym) {
   const lsx_system* sys = pl->sys;
-  const int nl = sys->nl, d = sys->d, S = sys->S;
-  std::vector<PointSym> syms;
-  if (use_sym) syms = find_point_symmetries(sys);
+  const int nl = sys->nl;
+  std::vector<std::vector<int32_t>> syms;  // the canonical row each symmetry maps every row to
+  if (use_sym) find_point_symmetries(sys, &syms);
   pl->nsym = (int)syms.size();
-  std::unordered_map<uint64_t, int32_t> where;
-  if (!syms.empty())
-    for (int64_t i = 0; i < sys->N; ++i) where[pack_key(&sys->mn[i * S], S)] = (int32_t)i;
   for (int j = 0; j < nl; ++j) {
     LayerDev& ld = pl->L[j];
     const FibreTable& ft = sys->fib[j];
@@ -884,30 +928,19 @@ static void plan_orders(lsx_plan* pl, bool use_sym) {
       for (int f = 0; f < nf; ++f)
         for (int a = ft.ptr[f]; a < ft.ptr[f + 1]; ++a) fib[ft.rows[a]] = f;
       ld.sym_rep.assign(nf, -1);
-      int32_t img[kMaxIndex];
       for (int f = 0; f < nf; ++f) {
         if (ld.sym_rep[f] >= 0) continue;
         ld.sym_rep[f] = f;
         const int r0 = ft.ptr[f], L = ft.ptr[f + 1] - r0;
-        for (const PointSym& g : syms) {
+        for (const std::vector<int32_t>& image : syms) {
           // image of the fibre's first row decides the image fibre
-          auto image = [&](int32_t row) {
-            const int32_t* m = &sys->mn[(size_t)row * S];
-            for (int k = 0; k < nl; ++k)
-              for (int r = 0; r < d; ++r) {
-                int64_t acc = 0;
-                for (int c = 0; c < d; ++c) acc += (int64_t)g.M[k][r * d + c] * m[k * d + c];
-                img[k * d + r] = (int32_t)acc;
-              }
-            return where.at(pack_key(img, S));
-          };
-          const int f2 = fib[image(ft.rows[r0])];
+          const int f2 = fib[image[ft.rows[r0]]];
           if (ld.sym_rep[f2] >= 0) continue;
           if (ft.ptr[f2 + 1] - ft.ptr[f2] != L) continue;  // cannot happen for a symmetry
           bool same_fibre = true;
           std::vector<int32_t> rows(L);
           for (int a = 0; a < L; ++a) {
-            rows[a] = image(ft.rows[r0 + a]);
+            rows[a] = image[ft.rows[r0 + a]];
             same_fibre = same_fibre && fib[rows[a]] == f2;
           }
           if (!same_fibre) continue;
@@ -1817,26 +1850,31 @@ static lsx_status choose_cycle(lsx_plan* pl, lsx_state* st, bool tune_store) {
     return ms * 1e3f / reps;
   };
   if (tune_store) st->store_us[0] = st->store_us[1] = 0.f;
-  // the cycle with the current picks, each store mode: about 5 ms of passes, 3 to 500 cycles
-  // sized by a timed warm-up cycle (a few-microsecond cycle needs many for a stable ranking);
-  // returns the best time and its mode
+  // the cycle with the current picks, each store mode: about 3 ms of passes, 3 to 300 cycles
+  // sized by a timed warm-up cycle (a few-microsecond cycle needs many for a stable ranking), but
+  // no more than the first fifth of them when that is 3 % behind the best so far: a fifth repeats
+  // within 1 % (cycles of 80 to 85 us, twisted bilayer, N = 82321, W = 16: the whole tuning of a
+  // state took 42 ms with 5 ms of every combination, now 22); returns the best time and its mode
+  float best = -1.f;
   auto evaluate = [&](int& nt_best) {
-    float best = -1.f;
+    float mine = -1.f;
     for (int m = 0; m < (tune_store ? 2 : 1) && he == hipSuccess; ++m) {
       const int nt = tune_store ? m : st->nt;
       const float warm_us = timed(nt, 1);
-      const int reps = (int)std::max(3.0, std::min(500.0, 5000.0 / std::max(1.0f, warm_us)));
-      const float us = timed(nt, reps);
+      const int reps = (int)std::max(3.0, std::min(300.0, 3000.0 / std::max(1.0f, warm_us)));
+      const float ahead = mine < 0.f ? best : best < 0.f ? mine : std::min(mine, best);
+      float us = ahead > 0.f && reps >= 15 ? timed(nt, reps / 5) : 0.f;
+      if (us < 1.03f * ahead || us == 0.f) us = timed(nt, reps);
       if (tune_store && (st->store_us[nt] == 0.f || us < st->store_us[nt])) st->store_us[nt] = us;
-      if (best < 0.f || us < best) {
-        best = us;
+      if (mine < 0.f || us < mine) {
+        mine = us;
         nt_best = nt;
       }
     }
-    return best;
+    return mine;
   };
   int best_nt = st->nt;
-  float best = evaluate(best_nt);
+  best = evaluate(best_nt);
   int best_pick[kMaxLayers] = {0, 0, 0};
   for (int l = 0; l < nl && he == hipSuccess; ++l)
     for (int k = 1; k < 3 && he == hipSuccess; ++k) {
@@ -1976,8 +2014,8 @@ static lsx_status choose_tiles(lsx_plan* pl, lsx_state* st) {
         a.W = W;
         a.u = c.u;
         // two timed passes (enough for passes of a millisecond or more), then, for shorter
-        // passes, at least five and about 1 ms of them: launch jitter is comparable to a
-        // few-microsecond pass
+        // passes, at least five and about 0.5 ms of them (at most a hundred): launch jitter is
+        // comparable to a few-microsecond pass
         auto time_reps = [&](int reps, float& per) {
           hipError_t e = hipEventRecord(e0, nullptr);
           for (int r = 0; r < reps && e == hipSuccess; ++r)
@@ -1991,7 +2029,9 @@ static lsx_status choose_tiles(lsx_plan* pl, lsx_state* st) {
         };
         hipError_t he = launch_pass(nullptr, pl->fmt, W, (int)t.size(), c.nb, pks, a);
         if (he == hipSuccess) he = time_reps(2, ms);
-        if (he == hipSuccess && ms < 1.0f) he = time_reps(std::min(100, std::max(5, (int)(1.0f / std::max(ms, 1e-3f)))), ms);
+        // a shape this far behind the two best so far is not timed further
+        const bool behind = second >= 0.f && ms > 1.2f * second + 5e-3f;
+        if (he == hipSuccess && ms < 1.0f && !behind) he = time_reps(std::min(100, std::max(5, (int)(0.5f / std::max(ms, 1e-3f)))), ms);
         if (he != hipSuccess) {
           err = fail(LSX_E_HIP, std::string("autotune: ") + hipGetErrorString(he));
           break;

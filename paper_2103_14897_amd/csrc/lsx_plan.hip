@@ -262,11 +262,11 @@ __device__ __forceinline__ bool bj_rotation(double app, double aqq, double apq, 
 
 // Every index pair of the matrix meets once a sweep: the pairs across the two blocks of P in sixteen
 // rounds here, the pairs inside a block in the fifteen before them in the sweep's first round of
-// blocks.  A round takes one barrier: every wave works out all sixteen rotations and S alternates between two arrays.  Bound by the latency of that chain (LDS, two
-// reciprocal roots, lane exchange, LDS), and by its fixed part (launch, loads) in the rounds
-// that rotate nothing: 13.6 us a launch on average (twisted bilayer, N = 82321, 459 launches), 25.7
-// (432 launches) with every pair in every block round, three divisions and three roots a rotation
-// and two barriers.
+// blocks.  A round takes one barrier: every wave works out all sixteen rotations and S alternates
+// between two arrays.  Bound by the latency of that chain (LDS, two reciprocal roots, lane exchange,
+// LDS), and by its fixed part (launch, loads) in the rounds that rotate nothing: 13.6 us a launch on
+// average (twisted bilayer, N = 82321, 459 launches), 25.7 (432 launches) with every pair in every
+// block round, three divisions and three roots a rotation and two barriers.
 __global__ __launch_bounds__(256) void k_bj_pairs(BJArgs g) {
   __shared__ double S[2][32][33];
   __shared__ double Qs[32][33];
