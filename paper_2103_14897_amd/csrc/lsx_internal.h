@@ -283,6 +283,7 @@ struct CopyItem {
   double2* to;
   int64_t elems;
 };
+hipError_t launch_gather_rows(hipStream_t s, int64_t N, const int32_t* pos, const double2* src, double2* dst);
 hipError_t launch_copy_home(hipStream_t s, int n, const CopyItem* items, int64_t max_elems);
 hipError_t launch_fibre_mass(hipStream_t s, int nf, const int32_t* ptr, const int32_t* rows, int W,
                              const double2* c, double* out);

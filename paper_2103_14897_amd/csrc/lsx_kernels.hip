@@ -740,13 +740,14 @@ __global__ __launch_bounds__(64 * KS) void k_gemv_orbit(PassArgs a) {
 // BF16x3), so the state operand of a k-step is the same for the whole wave: it is read once
 // per wave through the scalar cache instead of once per lane.  ORB: the tile
 // multiplies up to M fibres of a group with one propagator (PassArgs::orbit), else the tile's
-// own fibre.  Per fibre and row the products are summed in column order, then the KS waves in
-// order, so orbit and per-fibre tiles give identical results.  The k-steps run over the union
+// own fibre.  Per fibre and row the products are summed in column order, then the KS waves in a
+// fixed order, so orbit and per-fibre tiles give identical results.  The k-steps run over the union
 // of the four blocks' bands, and each block's lanes take zeros outside their own block's band.
 template <int KS, int FMT, int M, bool ORB, bool GATHER>
 __global__ __launch_bounds__(64 * KS) void k_gemv_rows(PassArgs a) {
   static_assert(ORB || M == 1, "a per-fibre tile has one fibre");
-  __shared__ double red[KS * M * 2 * 64];
+  constexpr int KR = KS > 4 ? 4 : KS;  // partial sums held at a time
+  __shared__ double red[KR * M * 2 * 64];
   const TileDesc t = a.tiles[blockIdx.x];
   if (t.f < 0) return;
   int nm = 1, r0[M];
@@ -830,15 +831,23 @@ __global__ __launch_bounds__(64 * KS) void k_gemv_rows(PassArgs a) {
     auto src = [&](int kk, int c) { return (rowok && 4 * kk >= qlo && 4 * kk < qhi) ? Pq + (int64_t)kk * 64 + 16 * c : zp; };
     // The state operand of a k-step: four consecutive rows of every fibre, one 64-byte read per
     // fibre where its rows are contiguous (no gather, k-step inside the fibre); columns past the
-    // fibre multiply zero padding and read the fibre's last row instead.  One k-step's loads in
-    // flight per wave (two measured slower: fewer waves fit).
+    // fibre multiply zero padding and read the fibre's last row instead.  The entries of the next
+    // k-step are loaded before this one's products (two steps ahead takes 87 registers and measured
+    // slower: fewer waves fit).  With that and half the LDS, which let a fourth workgroup of eight
+    // waves into a CU, a mixed FP32 pass of the twisted bilayer (N = 398821, 119 MB) takes 35.8 us, 40.3
+    // before.
     struct X4 {
       double2 v[4];
     };
+    PT f[4];  // the next k-step's entries
+#pragma unroll
+    for (int c = 0; c < 4; ++c) f[c] = *(klo + kw < khi ? src(klo + kw, c) : zp);
     for (int kk = klo + kw; kk < khi; kk += KS) {
       PT e[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) e[c] = *src(kk, c);
+      for (int c = 0; c < 4; ++c) e[c] = f[c];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) f[c] = *(kk + KS < khi ? src(kk + KS, c) : zp);
       if (!GATHER && 4 * kk + 3 < L) {
 #pragma unroll
         for (int m = 0; m < M; ++m) {
@@ -857,18 +866,34 @@ __global__ __launch_bounds__(64 * KS) void k_gemv_rows(PassArgs a) {
       }
     }
   }
+  if constexpr (KS > KR) {  // the upper waves' sums go to the lower ones first
+    if (kw >= KR)
 #pragma unroll
-  for (int m = 0; m < M; ++m) {
-    red[((kw * M + m) * 2 + 0) * 64 + lane] = yr[m];
-    red[((kw * M + m) * 2 + 1) * 64 + lane] = yi[m];
+      for (int m = 0; m < M; ++m) {
+        red[(((kw - KR) * M + m) * 2 + 0) * 64 + lane] = yr[m];
+        red[(((kw - KR) * M + m) * 2 + 1) * 64 + lane] = yi[m];
+      }
+    __syncthreads();
+    if (kw < KR)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        yr[m] += red[((kw * M + m) * 2 + 0) * 64 + lane];
+        yi[m] += red[((kw * M + m) * 2 + 1) * 64 + lane];
+      }
   }
+  if (kw < KR)
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      red[((kw * M + m) * 2 + 0) * 64 + lane] = yr[m];
+      red[((kw * M + m) * 2 + 1) * 64 + lane] = yi[m];
+    }
   __syncthreads();
   for (int idx = threadIdx.x; idx < 64 * M; idx += 64 * KS) {
     const int ln = idx & 63, m = idx >> 6;
     const int arow = 16 * (4 * t.rb + (ln >> 4)) + (ln & 15);
     if (m >= nm || arow >= L) continue;
     double sr = 0.0, si = 0.0;
-    for (int w = 0; w < KS; ++w) {
+    for (int w = 0; w < KR; ++w) {
       sr += red[((w * M + m) * 2 + 0) * 64 + ln];
       si += red[((w * M + m) * 2 + 1) * 64 + ln];
     }

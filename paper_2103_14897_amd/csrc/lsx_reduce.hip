@@ -43,6 +43,12 @@ __global__ __launch_bounds__(256) void k_copy_home(const CopyItem* items) {
     it.to[e] = it.from[e];
 }
 
+// A single state's rows in another order: dst[p] = src[pos[p]].
+__global__ __launch_bounds__(256) void k_gather_rows(int64_t N, const int32_t* pos, const double2* src, double2* dst) {
+  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (p < N) dst[p] = src[pos[p]];
+}
+
 // ---------------------------------------------------------------- FP64 reductions
 // Mass sum_i |c_iw|^2 and energy sum_i 1/2 |K_i|^2 |c_iw|^2 + Re conj(c_iw) (V c)_iw of every
 // column, as partial sums of one workgroup's rows.  V is Hermitian, so the terms of a coefficient
@@ -228,6 +234,12 @@ hipError_t launch_copy_home(hipStream_t s, int n, const CopyItem* items, int64_t
   const int64_t want = std::max<int64_t>(1, std::min<int64_t>((max_elems + 255) / 256, 4096 / n + 1));
   for (int i = 0; i < n; i += 65535)  // grid.y limit
     hipLaunchKernelGGL(k_copy_home, dim3((unsigned)want, (unsigned)std::min(65535, n - i)), dim3(256), 0, s, items + i);
+  return hipGetLastError();
+}
+
+hipError_t launch_gather_rows(hipStream_t s, int64_t N, const int32_t* pos, const double2* src, double2* dst) {
+  if (N == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, N, pos, src, dst);
   return hipGetLastError();
 }
 
