@@ -25,12 +25,16 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", os.path.
           # packed FP32 VALU forms are kept out of every code object
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 SOURCES = ["lsx_host.cpp", "lsx_kernels.hip", "lsx_rowsplit.hip", "lsx_plan.hip", "lsx_reduce.hip",
-           "lsx_resident.hip", "lsx_sample.hip"]
+           "lsx_resident.hip", "lsx_sample.hip", "lsx_mlp.hip"]
+
+# Options of single sources.  lsx_mlp.hip: the library tanh's two branches (the lanes of a wave take
+# both) become selects, with the same bits, so that independent evaluations overlap.
+EXTRA = {"lsx_mlp.hip": ["-mllvm", "-two-entry-phi-node-folding-threshold=100"]}
 
 
 def _compile(src):
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    cmd = ["hipcc", *COMMON, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = ["hipcc", *COMMON, *EXTRA.get(os.path.basename(src), []), "-c", os.path.join(CSRC, src), "-o", obj]
     if src.endswith(".hip"):
         cmd[1:1] = ["-x", "hip"]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -293,7 +293,7 @@ constexpr int64_t kStaticScratchDoubles = int64_t(1) << 20;  // 8 MiB per GPU
 constexpr int kMaxDevices = 64;
 hipError_t static_scratch(double** ptr);
 
-// ---------------------------------------------------------------- stochastic steps (lsx_sample.hip)
+// ---------------------------------------------------------------- stochastic steps (lsx_sample.hip, lsx_mlp.hip)
 hipError_t launch_si_step(hipStream_t s, const Sweep& sweep, int W, double tau, const double* K2, int nv1,
                           const int32_t* nbr1, const double2* v1, const double* wt1, const int32_t* fid1, int nv2,
                           const int32_t* nbr2, const double2* v2, const double* wt2, const int32_t* fid2,
