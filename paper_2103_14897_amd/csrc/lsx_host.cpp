@@ -957,12 +957,12 @@ static void plan_orders(lsx_plan* pl, bool use_sym) {
 // Matrices of more than this many rows (after the complex embedding) take the blocked solver, which
 // pads them to a multiple of 32 and runs in launches of a round each; the scalar one takes a single
 // launch and a workgroup a matrix.  Where a layer has longer ones, the short ones go through the
-// rounds that are launched anyway (twisted bilayer, N = 82321, plan: 42.0 ms with a line at 96 rows,
+// rounds that are launched anyway (twisted bilayer, N = 85261, plan: 42.0 ms with a line at 96 rows,
 // 37.9 at 32; N = 9061: 13.3 and 7.8); a layer without any stays scalar up to 64 rows (chain, N =
 // 1281: 1.8 ms, 2.1 in rounds).
 static constexpr int kBlockedMin = 32, kBlockedOnlyMin = 64;
 
-// Blocked two-sided Jacobi (see lsx_kernels.hip) of the matrices `sel` of a precompute batch:
+// Blocked two-sided Jacobi (see lsx_plan.hip) of the matrices `sel` of a precompute batch:
 // sweeps of round-robin block rounds until a sweep rotates nothing, at most maxsweeps; the
 // matrices that converge drop out after each sweep.  info[m] receives the sweeps of matrix m,
 // or -1 without convergence.
@@ -1853,7 +1853,7 @@ static lsx_status choose_cycle(lsx_plan* pl, lsx_state* st, bool tune_store) {
   // the cycle with the current picks, each store mode: about 3 ms of passes, 3 to 300 cycles
   // sized by a timed warm-up cycle (a few-microsecond cycle needs many for a stable ranking), but
   // no more than the first fifth of them when that is 3 % behind the best so far: a fifth repeats
-  // within 1 % (cycles of 80 to 85 us, twisted bilayer, N = 82321, W = 16: the whole tuning of a
+  // within 1 % (cycles of 80 to 85 us, twisted bilayer, N = 85261, W = 16: the whole tuning of a
   // state took 42 ms with 5 ms of every combination, now 22); returns the best time and its mode
   float best = -1.f;
   auto evaluate = [&](int& nt_best) {
@@ -2668,7 +2668,7 @@ extern "C" lsx_status lsx_observables(lsx_plan* pl, lsx_state* st, uint32_t mask
 
 // Allocation-free variant of lsx_observables: the state is a caller-owned device array, the
 // results stay on the device, and the reduction partials go to the static scratch array of
-// lsx_kernels.hip (one per GPU, shared by every call on that GPU).  The partials are written
+// lsx_reduce.hip (one per GPU, shared by every call on that GPU).  The partials are written
 // before they are read within a call, so nothing needs clearing; calls that overlap on one GPU
 // race on the array.  Same kernels, block count and fixed reduction order as lsx_observables,
 // so the two give identical values.

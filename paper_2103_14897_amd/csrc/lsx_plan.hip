@@ -265,7 +265,7 @@ __device__ __forceinline__ bool bj_rotation(double app, double aqq, double apq, 
 // blocks.  A round takes one barrier: every wave works out all sixteen rotations and S alternates
 // between two arrays.  Bound by the latency of that chain (LDS, two reciprocal roots, lane exchange,
 // LDS), and by its fixed part (launch, loads) in the rounds that rotate nothing: 13.6 us a launch on
-// average (twisted bilayer, N = 82321, 459 launches), 25.7 (432 launches) with every pair in every
+// average (twisted bilayer, N = 85261, 459 launches), 25.7 (432 launches) with every pair in every
 // block round, three divisions and three roots a rotation and two barriers.
 __global__ __launch_bounds__(256) void k_bj_pairs(BJArgs g) {
   __shared__ double S[2][32][33];
@@ -487,7 +487,7 @@ __global__ void k_eig_fn(int64_t nlam, const double* lam, double t, int flow, do
 // A contraction over the eigenvectors, on the FP64 matrix cores: a wave takes a 16-row block by 16
 // NB columns, with the entries' columns as the matrix rows and the entries' rows as the matrix columns,
 // so that C[4 r + l / 16][l % 16] of lane l is element l of chunk 4 cb + r of the stored order and both
-// operands are rows of V^T as they lie.  Twisted bilayer, N = 82321: 187 us a propagator set, 1.9 ms
+// operands are rows of V^T as they lie.  Twisted bilayer, N = 85261: 187 us a propagator set, 1.9 ms
 // with one entry a thread and no operand shared.
 template <int FMT, bool EMB>
 __device__ __forceinline__ void form_tile(const double* VT, const double2* gh, int n, int L, int rb, int cb0, char* P,
