@@ -3325,7 +3325,7 @@ struct lsx_sampler {
   int p[2] = {0, 0};
   double eps = 0.0;
   int nf[2] = {0, 0};
-  // W = 1: the launch bound (tiles of every fibre) and the tiles of the sampled fibres, per sub-step
+  // 16-row blocks of every fibre; W = 1: the launch bound, with the tiles of the sampled fibres
   int ntiles[2] = {0, 0};
   DBuf<TileDesc> tiles[2];
   DBuf<int32_t> off[2], fid[2], d0[2];
@@ -3533,6 +3533,25 @@ lsx_status apply_phase(lsx_plan* pl, lsx_state* st, const double2* ph, hipStream
   return LSX_OK;
 }
 
+// Waves that split the fibre length in the mixed formats' sampled passes (k_pass_slots), by the 16 x 16
+// tiles of a whole pass.  Each wave's FP32 sums cover other k-steps and the weights multiply their
+// rounding (two splits differ by 1e-8 of the state), so the split does not follow the state's timed
+// shape, which differs from one state to the next near a tie.  The lines lie where the fastest length
+// split of a whole FP32 pass changed when shapes were timed by states of 265 sizes (twisted bilayer,
+// kappa = 1, N = 2137 to 341053, W = 8 to 128): both layers split alike at 161 of the 181 sizes where
+// all states of a size agreed.  Four waves up to 8 tiles a CU, 16 where the column blocks go in pairs,
+// 20 for one or two column blocks (long fibres); two up to 72, then one; past 256 a CU shapes of two waves
+// were picked again.  BF16x3 chunks are eight k-steps long: four waves below two tiles a CU, else two.
+// A pinned or forced shape is followed (two waves for a row split).
+int slot_waves(const lsx_sampler* sm, int j) {
+  const lsx_state* st = sm->st;
+  if (!(st->tuned_us[j] > 0.f)) return st->ks[j] > 0 ? st->ks[j] : 2;
+  const int64_t wt = (st->W + 15) / 16, per_cu = sm->ntiles[j] * wt / 256;
+  if (sm->pl->fmt == PF_BF16X3) return per_cu < 2 ? 4 : 2;
+  if (per_cu < (wt <= 2 ? 20 : wt % 2 ? 8 : 16)) return 4;
+  return per_cu < 72 || per_cu >= 256 ? 2 : 1;
+}
+
 // One sampled sub-step of `layer` with propagators `half`, uniforms u [W][ustride].  pend: phase the
 // stored state still lacks (null: none).  The sampled passes of several wavepackets multiply it into
 // the few columns they read and take it off what they write; the other passes apply it first (pend
@@ -3610,7 +3629,7 @@ lsx_status sampled_substep(lsx_sampler* sm, int layer, int half, const double* u
   a.diag = pl->diag.p ? pl->diag.p + (size_t)((layer - 1) * 3 + half) * pl->sys->N : nullptr;
   a.zero = pl->zero.p;
   a.W = W;
-  LSX_HIP_TRY(launch_pass_slots(s, pl->fmt, sm->nunits[j], sm->maxslots[j], a));
+  LSX_HIP_TRY(launch_pass_slots(s, pl->fmt, sm->nunits[j], sm->maxslots[j], slot_waves(sm, j), a));
   return LSX_OK;
 }
 

@@ -201,8 +201,8 @@ struct SlotArgs {
   const void* zero = nullptr;
   int W = 0;
 };
-// max_slots: most slots a class can have
-hipError_t launch_pass_slots(hipStream_t s, int fmt, int nunits, int max_slots, const SlotArgs& a);
+// max_slots: most slots a class can have; ks: waves splitting the fibre length (1, 2 or 4)
+hipError_t launch_pass_slots(hipStream_t s, int fmt, int nunits, int max_slots, int ks, const SlotArgs& a);
 // row-split tiles (lsx_rowsplit.hip): ms waves on consecutive row blocks of 16 nb columns
 hipError_t launch_rowsplit(hipStream_t s, int fmt, int ntiles, int nb, int ms, const PassArgs& a);
 // Batched launches with a.persist set: computes (once per kernel) the persistent grid of the pass

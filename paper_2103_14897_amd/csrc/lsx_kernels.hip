@@ -355,15 +355,18 @@ __global__ LSX_MFMA_BOUNDS(64 * KS, NB == 1) void k_pass_bf16x3_persist(PassArgs
 // Weighted fibre increments x + g (P_f x - x) of the drawn (fibre, wavepacket) pairs, from the
 // compacted columns of every class of fibres with one propagator (SlotArgs), written straight into
 // the state.  A workgroup takes one 16-row block of a class's propagator and all of the class's
-// slots, 32 at a time; its KS waves split the fibre length as in the passes above.
+// slots, 32 at a time; its KS waves split the fibre length in groups of U k-steps as in the passes
+// above.  The weights, tens at a time, multiply the rounding of the mixed formats' FP32 sums, so which
+// k-steps a sum covers shows in the result (1e-8 of the state): KS and U are those of a K-split pass of
+// the state's size.
 // Bound by reading the propagators (253 MB twice at most, at 16 draws for each of 128 wavepackets of
 // the twisted bilayer, kappa = 1, N = 398821): 123 us a pass and 32 for the compaction.  Tiles of
 // single fibres read a shared propagator once per drawn fibre (889 fibres share 58 of them) for 2.3
 // drawn columns of 16 on average, on a grid sized for every fibre and column, and wrote a second
 // array that was copied back: 650 to 790 us and 330.
-template <int FMT, int KS>
+template <int FMT, int KS, int U>
 __global__ LSX_MFMA_BOUNDS(64 * KS, FMT != PF_BF16X3) void k_pass_slots(SlotArgs a) {
-  constexpr int NB = 2, U = 2;
+  constexpr int NB = 2;
   extern __shared__ double red[];
   const SlotUnit t = a.units[blockIdx.x];
   const int n = a.n[t.cls], L = t.L;
@@ -996,22 +999,40 @@ static hipError_t launch_mfma(hipStream_t s, int fmt, int ntiles, const PassArgs
                 : launch_mfma_g<NB, KS, false>(s, fmt, ntiles, a, batched);
 }
 
-hipError_t launch_pass_slots(hipStream_t s, int fmt, int nunits, int max_slots, const SlotArgs& a) {
-  if (nunits == 0) return hipSuccess;
-  constexpr int KS = 4, NB = 2;
+template <int FMT, int KS, int U>
+static hipError_t launch_slots_k(hipStream_t s, int nunits, int max_slots, const SlotArgs& a) {
+  constexpr int NB = 2;
   const size_t shm = (size_t)KS * NB * 2 * 4 * 64 * sizeof(double);
-  // few classes of many slots: their 32-slot blocks go to workgroups of their own, up to 16
-  // workgroups a compute unit (1660 units, up to 2048 slots: 138 us a pass with one workgroup a unit,
+  // few classes of many slots: their 32-slot blocks go to workgroups of their own, up to 64 waves a
+  // compute unit (1660 units of four waves, up to 2048 slots: 138 us a pass with one workgroup a unit,
   // 123 with two); with many classes a class has few slots and one workgroup takes them
-  const int64_t want = std::max(1, 4096 / nunits), most = ((int64_t)max_slots + 16 * NB - 1) / (16 * NB);
+  const int64_t want = std::max(1, 16384 / (KS * nunits)), most = ((int64_t)max_slots + 16 * NB - 1) / (16 * NB);
   const dim3 g(nunits, (unsigned)std::max<int64_t>(1, std::min(want, most)));
-  if (fmt == PF_F64)
-    hipLaunchKernelGGL((k_pass_slots<PF_F64, KS>), g, dim3(64 * KS), shm, s, a);
-  else if (fmt == PF_F32)
-    hipLaunchKernelGGL((k_pass_slots<PF_F32, KS>), g, dim3(64 * KS), shm, s, a);
-  else
-    hipLaunchKernelGGL((k_pass_slots<PF_BF16X3, KS>), g, dim3(64 * KS), shm, s, a);
+  hipLaunchKernelGGL((k_pass_slots<FMT, KS, U>), g, dim3(64 * KS), shm, s, a);
   return hipGetLastError();
+}
+
+template <int KS>
+static hipError_t launch_slots_mix(hipStream_t s, int fmt, int nunits, int max_slots, const SlotArgs& a) {
+  if (fmt == PF_BF16X3) return launch_slots_k<PF_BF16X3, KS, 1>(s, nunits, max_slots, a);
+  switch (prefetch_depth()) {
+    case 1: return launch_slots_k<PF_F32, KS, 1>(s, nunits, max_slots, a);
+    case 4: return launch_slots_k<PF_F32, KS, 4>(s, nunits, max_slots, a);
+    default: return launch_slots_k<PF_F32, KS, 2>(s, nunits, max_slots, a);
+  }
+}
+
+// ks: waves that split the fibre length (mixed formats).  FP64 sums round at 1e-16 however they are
+// split, and four waves are the fastest.
+hipError_t launch_pass_slots(hipStream_t s, int fmt, int nunits, int max_slots, int ks, const SlotArgs& a) {
+  if (nunits == 0) return hipSuccess;
+  if (fmt == PF_F64) return launch_slots_k<PF_F64, 4, 2>(s, nunits, max_slots, a);
+  switch (ks) {
+    case 1: return launch_slots_mix<1>(s, fmt, nunits, max_slots, a);
+    case 2: return launch_slots_mix<2>(s, fmt, nunits, max_slots, a);
+    case 4: return launch_slots_mix<4>(s, fmt, nunits, max_slots, a);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 template <int KS, bool B>
