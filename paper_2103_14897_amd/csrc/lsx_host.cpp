@@ -2751,16 +2751,15 @@ static const int32_t* layout_table(const lsx_plan* pl, int layer, int layout) {
   return layout_map(pl, layer, layout);
 }
 
-// the systems' copies from work array to state array, for the arrays they have now
-static lsx_status batch_home(lsx_batch* b) {
+// Writes the systems' copies from work array to state array, for the arrays they have now, into the
+// table that lsx_batch_create allocated: on the call's stream, behind the launches that still read
+// it, and complete on return (the host vector ends here).
+static lsx_status batch_home(lsx_batch* b, hipStream_t s) {
   std::vector<CopyItem> v;
-  b->home_max = 0;
-  for (const lsx_state* st : b->st) {
-    const int64_t n = st->plan->sys->N * st->W;
-    v.push_back({st->buf[1], st->buf[0], n});
-    b->home_max = std::max(b->home_max, n);
-  }
-  return b->home.upload(v, nullptr);
+  for (const lsx_state* st : b->st) v.push_back({st->buf[1], st->buf[0], st->plan->sys->N * st->W});
+  LSX_HIP_TRY(hipMemcpyAsync(b->home.p, v.data(), v.size() * sizeof(CopyItem), hipMemcpyHostToDevice, s));
+  LSX_HIP_TRY(hipStreamSynchronize(s));
+  return LSX_OK;
 }
 
 // replays still running finish first
@@ -3047,7 +3046,9 @@ extern "C" lsx_status lsx_batch_create(lsx_plan* const* plans, lsx_state* const*
         if (prepare_persistent(b->fmt, b->w1 ? 1 : 2, b->nb[layer - 1], b->ks[layer - 1], a0) != hipSuccess)
           return cleanup(fail(LSX_E_HIP, "persistent launch setup failed"));
       }
-  if ((e = batch_home(b)) != LSX_OK) return cleanup(e);
+  if ((e = b->home.alloc(b->st.size())) != LSX_OK) return cleanup(e);
+  if ((e = batch_home(b, nullptr)) != LSX_OK) return cleanup(e);
+  for (const lsx_state* st : b->st) b->home_max = std::max(b->home_max, st->plan->sys->N * st->W);
   if (hipDeviceSynchronize() != hipSuccess) return cleanup(fail(LSX_E_HIP, "batch setup failed"));
   for (lsx_state* st : b->st) st->nbatches++;
   for (lsx_state* st : b->st) b->bufs.emplace_back(st->buf[0], st->buf[1]);
@@ -3065,8 +3066,9 @@ extern "C" lsx_status lsx_batch_step(lsx_batch* b, int64_t nsteps, void* stream)
     if (b->bufs[i].first != b->st[i]->buf[0] || b->bufs[i].second != b->st[i]->buf[1]) {
       b->args.clear();
       batch_drop_graph(b);
+      LSX_TRY(batch_home(b, s));
+      // last, so that a call after a failed one writes the table again
       for (size_t j = 0; j < b->st.size(); ++j) b->bufs[j] = {b->st[j]->buf[0], b->st[j]->buf[1]};
-      LSX_TRY(batch_home(b));
       break;
     }
   std::vector<PassSpec> head, body, tail;
