@@ -309,8 +309,9 @@ lsx_status lsx_plan_destroy(lsx_plan* plan);
  *            aligned) that the state wraps; the caller keeps it alive until
  *            lsx_state_destroy.  Its contents are the state.
  * The library also allocates one same-size work array per state (ping-pong
- * target of the fibre passes; a second one for a wrapped state where memory
- * allows, so that an odd number of passes needs no copy) and small reduction buffers.
+ * target of the fibre passes) and small reduction buffers.  A wrapped state takes a second
+ * work array, so that an odd number of passes needs no copy, where that is at most a
+ * sixteenth of the free memory and can be had; nothing else depends on it.
  */
 lsx_status lsx_state_create(lsx_plan* plan, int32_t W, void* dev_ptr, lsx_state** out);
 

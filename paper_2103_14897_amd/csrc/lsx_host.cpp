@@ -82,19 +82,24 @@ struct DBuf {
     p = nullptr;
     n = 0;
   }
-  lsx_status alloc(size_t count) {
+  // false without memory for it (or an injected failure, LSX_TEST_FAIL_ALLOC); sets no error
+  bool try_alloc(size_t count) {
     release();
     if (count == 0) count = 1;
-    if (test_fail_alloc()) return fail(LSX_E_OOM, "injected allocation failure (LSX_TEST_FAIL_ALLOC)");
+    if (test_fail_alloc()) return false;
     if (hipMalloc(reinterpret_cast<void**>(&p), count * sizeof(T)) != hipSuccess) {
       (void)hipGetLastError();
       p = nullptr;
-      return fail(LSX_E_OOM, "hipMalloc of " + std::to_string(count * sizeof(T)) + " bytes failed");
+      return false;
     }
     n = count;
     g_live_buffers++;
     g_live_bytes += (int64_t)(n * sizeof(T));
-    return LSX_OK;
+    return true;
+  }
+  lsx_status alloc(size_t count) {
+    if (try_alloc(count)) return LSX_OK;
+    return fail(LSX_E_OOM, "device allocation of " + std::to_string(count * sizeof(T)) + " bytes failed");
   }
   // Set-up copy from a host vector, complete on return: callers pass locals and temporaries,
   // so the copy must not outlive `v`, whatever HIP does with pageable memory.
@@ -1786,7 +1791,7 @@ static lsx_status choose_cycle(lsx_plan* pl, lsx_state* st, bool tune_store) {
   const int nl = pl->sys->nl, W = st->W;
   const int64_t N = pl->sys->N;
   DBuf<double2> tmp;
-  if (tmp.alloc((size_t)N * W) != LSX_OK) return LSX_OK;
+  if (!tmp.try_alloc((size_t)N * W)) return LSX_OK;
   PassArgs a[kMaxLayers];
   for (int layer = 1; layer <= nl; ++layer) {
     const LayerDev& ld = pl->L[layer - 1];
@@ -2109,10 +2114,6 @@ extern "C" lsx_status lsx_state_create(lsx_plan* pl, int32_t W, void* dev_ptr, l
   }
   if ((e = st->work.alloc(total)) != LSX_OK) return cleanup(e);
   st->buf[1] = st->work.p;
-  // a state whose arrays cannot swap roles would copy its result home after an odd number of
-  // passes (0.33 of the twisted bilayer's 9.6 ms for two FP64 steps, 0.35 of the trilayer's 3.1 ms for
-  // one FP32 step at W = 128)
-  if (dev_ptr && st->work2.alloc(total) == LSX_OK) st->buf[2] = st->work2.p;
   if ((e = choose_tiles(pl, st)) != LSX_OK) return cleanup(e);
   st->nred = (int)std::max<int64_t>(1, std::min<int64_t>(1024, (N + 255) / 256));
   // observables: mass, energy and the fibre masses of every layer in one result block
@@ -2120,6 +2121,15 @@ extern "C" lsx_status lsx_state_create(lsx_plan* pl, int32_t W, void* dev_ptr, l
   for (int j = 0; j < pl->sys->nl; ++j) nfsum += (size_t)pl->L[j].nf;
   if ((e = st->partial.alloc((size_t)2 * st->nred * W)) != LSX_OK) return cleanup(e);
   if ((e = st->result.alloc((size_t)W * (2 + std::max<size_t>(nfsum, 1)))) != LSX_OK) return cleanup(e);
+  // A state whose arrays cannot swap roles copies its result home after an odd number of passes (0.33
+  // of the twisted bilayer's 9.6 ms for two FP64 steps, 0.35 of the trilayer's 3.1 ms for one FP32 step
+  // at W = 128) unless it has a second work array.  Nothing needs it, so it is taken last, after
+  // everything that creation cannot do without, and only where it is a sixteenth of the free memory
+  // at most: what a program allocates afterwards finds nearly all that it would have found.
+  size_t mem_free = 0, mem_total = 0;
+  if (dev_ptr && hipMemGetInfo(&mem_free, &mem_total) == hipSuccess && total * sizeof(double2) <= mem_free / 16 &&
+      st->work2.try_alloc(total))
+    st->buf[2] = st->work2.p;
   if (hipDeviceSynchronize() != hipSuccess) return cleanup(fail(LSX_E_HIP, "state setup failed"));
   pl->nstates++;
   *out = st;
