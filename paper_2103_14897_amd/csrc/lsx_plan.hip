@@ -229,8 +229,9 @@ __global__ __launch_bounds__(1024) void k_bj_init(BJArgs g, const int32_t* sel) 
   if (threadIdx.x == 0) g.tiny[m] = 1e-16 * normF;
 }
 
-// 1 / sqrt(x) for x in [0.25, 8): the hardware estimate with one third-order and one second-order
-// correction.
+// 1 / sqrt(x) for x in [0.25, 8): the hardware estimate y0, with e = 1 - x y0^2 corrected by the binomial
+// series of (1 - e)^(-1/2) to second order, 1 + e / 2 + 3 e^2 / 8, and then by one Newton step,
+// 1 + e / 2.
 __device__ __forceinline__ double rsqrt_f64(double x) {
   double y = __builtin_amdgcn_rsq(x);
   double e = fma(-x * y, y, 1.0);
@@ -270,7 +271,7 @@ __device__ __forceinline__ bool bj_rotation(double app, double aqq, double apq, 
 __global__ __launch_bounds__(256) void k_bj_pairs(BJArgs g) {
   __shared__ double S[2][32][33];
   __shared__ double Qs[32][33];
-  const int i = blockIdx.x, a = blockIdx.y;
+  const int a = blockIdx.x, i = blockIdx.y;
   const int m = g.mat[a];
   const int n = g.ndim[m];
   if (i >= n >> 5) return;
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(256) void k_bj_pairs(BJArgs g) {
 // operands of the second product Q_P^T X.
 __global__ LSX_MFMA_BOUNDS(256, true) void k_bj_tiles(BJArgs g) {
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int t = blockIdx.x * 4 + wv, a = blockIdx.y;
+  const int t = blockIdx.y * 4 + wv, a = blockIdx.x;
   const int m = g.mat[a];
   const int n = g.ndim[m], nb = n >> 4, np = nb >> 1;
   if (t >= 2 * np * np) return;
@@ -436,11 +437,13 @@ hipError_t launch_bj_init(hipStream_t s, int nsel, const int32_t* sel, const BJA
 
 hipError_t launch_bj_round(hipStream_t s, int count, int maxn, const BJArgs& g) {
   if (count == 0) return hipSuccess;
+  // Matrices in x: their number has no bound below x's, where y and z end at 65535.  The pairs of a
+  // matrix of 8192 rows (the most precompute_layer takes) are 256, its workgroups of tiles 32768.
   const int np = maxn / 32;
-  hipLaunchKernelGGL(k_bj_pairs, dim3(np, count), dim3(256), 0, s, g);
+  hipLaunchKernelGGL(k_bj_pairs, dim3(count, np), dim3(256), 0, s, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_bj_tiles, dim3((2 * np * np + 3) / 4, count), dim3(256), 0, s, g);
+  hipLaunchKernelGGL(k_bj_tiles, dim3(count, (2 * np * np + 3) / 4), dim3(256), 0, s, g);
   return hipGetLastError();
 }
 
