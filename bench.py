@@ -37,16 +37,26 @@ HBM_PEAK = 8.0e12
 # complex128; mixed: off-diagonal E in complex64 or three bf16 terms x (re, im))
 PROP_BYTES = {"fp64": 16, "mix_fp32": 8, "mix_bf16x3": 12}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "fibre_pass_chain_Ec2e4_W64_traffic.json")
-KERNEL_SRC = os.path.join(ROOT, "paper_2103_14897_amd", "csrc", "lsx_kernels.hip")
+# every source that a fibre pass is compiled from
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2103_14897_amd", "csrc", f)
+               for f in ("lsx_internal.h", "lsx_kernels.hip", "lsx_pass.h", "lsx_rowsplit.hip")]
+
+
+def kernel_source_hash():
+    import hashlib
+    h = hashlib.sha256()
+    for f in KERNEL_SRCS:
+        with open(f, "rb") as src:
+            h.update(hashlib.sha256(src.read()).digest())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic(path):
     """HBM bytes per launch of the layer-2 pass from the committed rocprofv3 counters,
-    or None when the kernel source has changed since they were taken."""
-    import hashlib
+    or None when a kernel source has changed since they were taken."""
     try:
         rec = json.load(open(TRAFFIC_FILE))
-        h = hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()[:16]
+        h = kernel_source_hash()
     except OSError:
         return None
     if rec.get("kernel_source_sha256_16") != h or path not in rec.get("layer2_pass", {}):
