@@ -27,20 +27,24 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", os.path.
 SOURCES = ["lsx_host.cpp", "lsx_kernels.hip", "lsx_rowsplit.hip", "lsx_plan.hip", "lsx_reduce.hip",
            "lsx_resident.hip", "lsx_sample.hip", "lsx_mlp.hip"]
 
-# Options of single sources.  lsx_mlp.hip: the library tanh's two branches (the lanes of a wave take
+# Options of single sources, left out where the compiler does not know them (they are internal to
+# LLVM and change no result).  lsx_mlp.hip: the library tanh's two branches (the lanes of a wave take
 # both) become selects, with the same bits, so that independent evaluations overlap.
 EXTRA = {"lsx_mlp.hip": ["-mllvm", "-two-entry-phi-node-folding-threshold=100"]}
 
 
 def _compile(src):
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    cmd = ["hipcc", *COMMON, *EXTRA.get(os.path.basename(src), []), "-c", os.path.join(CSRC, src), "-o", obj]
-    if src.endswith(".hip"):
-        cmd[1:1] = ["-x", "hip"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
-    return obj
+    extra = EXTRA.get(os.path.basename(src), [])
+    lang = ["-x", "hip"] if src.endswith(".hip") else []
+    for opts in ([extra, []] if extra else [[]]):
+        cmd = ["hipcc", *lang, *COMMON, *opts, "-c", os.path.join(CSRC, src), "-o", obj]
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        if r.returncode == 0:
+            return obj
+        if opts:
+            print(f"{src}: built without {' '.join(opts)}", file=sys.stderr)
+    raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
 
 
 def build(verbose=False):
