@@ -684,7 +684,7 @@ struct lsx_plan {
   DBuf<int32_t> xmap[kMaxLayers][kMaxLayers];
   DBuf<int32_t> iota;  // identity table (batched gathers over systems whose table is the identity)
   int nsym = 0;        // point symmetries the propagators are shared over (identity excluded)
-  DBuf<double2> zero;  // 1 KiB of zeros (out-of-range operand loads of the passes)
+  DBuf<double2> zero;  // kZeroBytes of zeros (out-of-range operand loads of the passes)
   LayerDev L[kMaxLayers];
   // row parts of the kernels that read potential neighbours, and their row list
   Sweep sweep;
@@ -1030,7 +1030,8 @@ static lsx_status block_jacobi(hipStream_t s, const std::vector<int32_t>& sel, c
   return LSX_OK;
 }
 
-// Resident steps hold two copies of a column in LDS: 2048 rows are 64 KB.
+// Resident steps hold two copies of a column in LDS: 2048 rows are 64 KB.  kResidentBytes ends before
+// that (512 rows, 1536 where only the diagonal blocks of a mixed path are multiplied).
 static constexpr int64_t kResidentMaxRows = 2048;
 // Row table of the resident steps and the propagator bytes a pass reads per column.
 static lsx_status resident_rows(lsx_plan* pl, int layer, hipStream_t s) {
@@ -1427,7 +1428,7 @@ static lsx_status plan_create(lsx_system* sys, double tau, int32_t scheme, doubl
         for (int64_t p = 0; p < sys->N; ++p) x[p] = pos[k][pl->L[j].h_rows[p]];
         if ((st = pl->xmap[j][k].upload(x, s)) != LSX_OK) return cleanup(st);
       }
-    if ((st = pl->zero.upload(std::vector<double2>(64, make_double2(0.0, 0.0)), s)) != LSX_OK) return cleanup(st);
+    if ((st = pl->zero.upload(std::vector<double2>(kZeroBytes / sizeof(double2), make_double2(0.0, 0.0)), s)) != LSX_OK) return cleanup(st);
   }
   if (kappa != 0.0) {
     const SchemeTimes times = scheme_times(scheme, tau, nl);
@@ -1855,11 +1856,13 @@ static lsx_status choose_cycle(lsx_plan* pl, lsx_state* st, bool tune_store) {
     return ms * 1e3f / reps;
   };
   if (tune_store) st->store_us[0] = st->store_us[1] = 0.f;
-  // the cycle with the current picks, each store mode: about 3 ms of passes, 3 to 300 cycles
+  // The cycle with the current picks, each store mode: about 3 ms of passes, 3 to 300 cycles
   // sized by a timed warm-up cycle (a few-microsecond cycle needs many for a stable ranking), but
-  // no more than the first fifth of them when that is 3 % behind the best so far: a fifth repeats
-  // within 1 % (cycles of 80 to 85 us, twisted bilayer, N = 85261, W = 16: the whole tuning of a
-  // state took 42 ms with 5 ms of every combination, now 22); returns the best time and its mode
+  // no more than the first fifth of them when that is 3 % behind the best so far (twisted bilayer, N =
+  // 85261, W = 16: the whole tuning of a state took 42 ms with 5 ms of every combination, now 22).  Ten
+  // fresh states' steps lie within 4 % of each other, 5 % with the longer timing, and within 2 % in most
+  // systems (chains N = 1281, 5149 and 25003, twisted bilayers N = 9061 and 36937, every precision, 6 to 37
+  // us a step): picks that close change places.  Returns the best time and its mode.
   float best = -1.f;
   auto evaluate = [&](int& nt_best) {
     float mine = -1.f;

@@ -83,6 +83,10 @@ constexpr int kOrbitStride = 1 + kOrbitMax;
 constexpr int kOrbitNB = 8;
 
 struct PassArgs;
+// Size of a plan's buffer of zeros: the widest load from it is a 16-byte operand for each of the 64 lanes
+// (the row-split passes read it at the lane, as they read a propagator chunk).
+constexpr int kZeroBytes = 64 * 16;
+
 // Arguments of every fibre-pass kernel.  Element k of fibre f (fibre position
 // p = r0 + k) is row in_pos[p] of X and row out_pos[p] of Y (identity when null),
 // so a pass can read one array layout and write another.
@@ -98,7 +102,7 @@ struct PassArgs {
   const double2* diag = nullptr;    // mixed formats: diagonal of P at fibre position p
   const double2* X = nullptr;       // input state  [rows][W]
   double2* Y = nullptr;             // output state [rows][W]
-  const void* zero = nullptr;       // >= 256 zero bytes: target of every out-of-range operand load
+  const void* zero = nullptr;       // kZeroBytes zero bytes: target of every out-of-range operand load
   const PassArgs* batch = nullptr;  // batched launches: per-system arguments, indexed by TileDesc::f
   const double* wt = nullptr;       // weighted single-state passes: [fibre] increment weights
   const int32_t* tcount = nullptr;  // device tile count: workgroups at or past it exit

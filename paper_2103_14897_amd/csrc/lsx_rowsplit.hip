@@ -76,6 +76,7 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f32m(PassArgs a) {
   TileDesc t = t0;
   t.rb = t0.rb * MS + kw;
   const bool act = t.rb < ((L + 15) >> 4);
+  static_assert(64 * sizeof(float2) <= kZeroBytes, "load_p reads a zero for every lane");
   const float2* zp = reinterpret_cast<const float2*>(a.zero);
   const float2* P = reinterpret_cast<const float2*>(reinterpret_cast<const char*>(a.P) + t.poff) +
                     (int64_t)(act ? t.rb : 0) * nks * 64;
@@ -196,6 +197,7 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f64m(PassArgs a) {
   TileDesc t = t0;
   t.rb = t0.rb * MS + kw;
   const bool act = t.rb < ((L + 15) >> 4);
+  static_assert(64 * sizeof(double2) <= kZeroBytes, "load_p reads a zero for every lane");
   const double2* zp = reinterpret_cast<const double2*>(a.zero);
   const double2* P = reinterpret_cast<const double2*>(reinterpret_cast<const char*>(a.P) + t.poff) +
                      (int64_t)(act ? t.rb : 0) * nks * 64;
@@ -326,6 +328,7 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_bf16m(PassArgs a) {
   TileDesc t = t0;
   t.rb = t0.rb * MS + kw;
   const bool act = t.rb < ((L + 15) >> 4);
+  static_assert(64 * sizeof(v8bf) <= kZeroBytes, "load_e reads a zero for every lane");
   const v8bf* zb = reinterpret_cast<const v8bf*>(a.zero);
   const v8bf* P = reinterpret_cast<const v8bf*>(reinterpret_cast<const char*>(a.P) + t.poff) +
                   (int64_t)(act ? t.rb : 0) * nkc * 6 * 64;
