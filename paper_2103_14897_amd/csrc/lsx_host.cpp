@@ -2274,6 +2274,7 @@ struct Runner {
   hipStream_t s;
   int cur = 0;
   int lay = 0;  // layout of buf[cur]; 0 = canonical
+  bool gathered = false;  // the state was put into the first pass's order by a launch of its own
 
   const int32_t* table(int layer, int layout) const { return layout_map(pl, layer, layout); }
 
@@ -2300,6 +2301,7 @@ struct Runner {
       LSX_HIP_TRY(launch_gather_rows(s, pl->sys->N, table(layer, lay), st->buf[cur], st->buf[to]));
       cur = to;
       lay = layer;
+      gathered = true;
     }
     PassArgs a;
     a.tiles = st->tiles[layer - 1].p;
@@ -2333,10 +2335,12 @@ struct Runner {
   }
   lsx_status finish() {
     if (cur != 0) {
-      if (st->owns0) {
+      if (st->owns0 && !gathered) {
         // both arrays belong to the library: swap roles instead of copying
         std::swap(st->buf[0], st->buf[1]);
       } else {
+        // an owned state that was reordered first ran an even number of passes: without the reordering
+        // its arrays would keep their roles, which a caller's captured graph of the call relies on
         LSX_HIP_TRY(hipMemcpyAsync(st->buf[0], st->buf[cur], (size_t)pl->sys->N * st->W * sizeof(double2),
                                    hipMemcpyDeviceToDevice, s));
       }
