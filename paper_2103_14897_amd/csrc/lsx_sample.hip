@@ -24,7 +24,7 @@ namespace lsx {
 // between a neighbour's first and last use then fit in that XCD's own L2, which the output of a
 // large state does not displace (non-temporal stores).  Twisted bilayer, N = 398821, W = 128: 0.93
 // ms a step in contiguous slabs with 8-column sweeps and ordinary stores, 0.87 ms now, 1.9 of 4.9
-// TB/s of state read and written once; L2 read misses (34 to 22 million lines) bound it.
+// TB/s of state read and written once; L2 read misses (34 to 22 million lines, 2.85 GB) bound it.
 // Measured and not used: the next row's indices loaded ahead of the current row's values (0.98 ms).
 //
 // Stencil sizes NV1, NV2 are compile-time for the common cases (1D cosine: 2, 2D first shell:
@@ -419,11 +419,34 @@ static unsigned grid_for(int64_t n, int64_t cap) {
   return (unsigned)(g < 1 ? 1 : (g > cap ? cap : g));
 }
 
-hipError_t launch_si_step(hipStream_t s, const Sweep& sweep, int W, double tau, const double* K2, int nv1,
+// Whether a semi-implicit step takes the row parts (Sweep::order) in sweeps of up to 32 columns with
+// non-temporal output, or slabs of the canonical order in sweeps of 8 with ordinary stores.  The state and
+// its output stay in the 256 MB last-level cache up to about 144 MB each, and there ordinary stores are
+// the faster ones; beyond it the parts are, where most lanes of their sweeps have a column.  Rows of a
+// number of columns that is no multiple of 8 do not fill whole lines, and their 8-column sweeps share a
+// line each: there the parts pay at almost any size.  Microseconds a step, slabs / parts, N = 58837, 150193
+// and 398821: W = 16 14.0 / 15.4, 28.7 / 34.1, 77 / 84; W = 48 36.5 / 47.6, 85 / 118, 312 / 342; W = 64 46.7 /
+// 51.4, 140 / 134, 423 / 397; W = 128 95 / 101, 303 / 290, 842 / 784.  N = 150193 and 398821: W = 31 86 / 65,
+// 335 / 193; W = 127 515 / 345, 1728 / 964; W = 36 80 / 122, 316 / 350.  Every element is summed alike on both
+// ways.
+static bool si_parts(int64_t N, int W) {
+  const int cw = W > 16 ? kSweepCW : 16, blocks = (W + cw - 1) / cw;
+  const double bytes = 16.0 * (double)N * W, lanes = (double)W / (cw * blocks);
+  if (W % 8 == 0) return W >= kSweepCW && bytes >= 144e6 && lanes >= 0.9;
+  return W > 8 && (W < 16 || lanes >= 0.75 || (W % 4 != 0 && bytes >= (W < kSweepCW ? 60e6 : 96e6)));
+}
+
+hipError_t launch_si_step(hipStream_t s, const Sweep& rows, int W, double tau, const double* K2, int nv1,
                           const int32_t* nbr1, const double2* v1, const double* wt1, const int32_t* fid1, int nv2,
                           const int32_t* nbr2, const double2* v2, const double* wt2, const int32_t* fid2,
                           const double2* X, double2* Y, const double2* zero) {
-  if (sweep.start[8] == 0) return hipSuccess;
+  const int64_t N = rows.start[8];
+  if (N == 0) return hipSuccess;
+  Sweep sweep = rows;
+  if (sweep.order && !si_parts(N, W)) {
+    sweep.order = nullptr;
+    for (int x = 0; x <= 8; ++x) sweep.start[x] = (int32_t)std::min(N, x * ((N + 7) / 8));
+  }
   // column block: LSX_SI_CW (1..256, a power of two) or the sweep's; 256 workgroups per XCD
   static const int cw_env = [] {
     const char* v = std::getenv("LSX_SI_CW");
