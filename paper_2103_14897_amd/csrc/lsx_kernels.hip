@@ -749,8 +749,9 @@ __global__ __launch_bounds__(64 * KS) void k_gemv_orbit(PassArgs a) {
 template <int KS, int FMT, int M, bool ORB, bool GATHER>
 __global__ __launch_bounds__(64 * KS) void k_gemv_rows(PassArgs a) {
   static_assert(ORB || M == 1, "a per-fibre tile has one fibre");
-  constexpr int KR = KS > 4 ? 4 : KS;  // partial sums held at a time
-  __shared__ double red[KR * M * 2 * 64];
+  constexpr int KR = KS > 4 ? 4 : KS;   // the waves' sums are added as pairs KR apart, then in order
+  constexpr int KH = ORB ? KR : KS;     // sums held at a time
+  __shared__ double red[KH * M * 2 * 64];
   const TileDesc t = a.tiles[blockIdx.x];
   if (t.f < 0) return;
   int nm = 1, r0[M];
@@ -843,14 +844,16 @@ __global__ __launch_bounds__(64 * KS) void k_gemv_rows(PassArgs a) {
       double2 v[4];
     };
     PT f[4];  // the next k-step's entries
+    if constexpr (ORB)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) f[c] = *(klo + kw < khi ? src(klo + kw, c) : zp);
+      for (int c = 0; c < 4; ++c) f[c] = *(klo + kw < khi ? src(klo + kw, c) : zp);
     for (int kk = klo + kw; kk < khi; kk += KS) {
       PT e[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) e[c] = f[c];
+      for (int c = 0; c < 4; ++c) e[c] = ORB ? f[c] : *src(kk, c);
+      if constexpr (ORB)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) f[c] = *(kk + KS < khi ? src(kk + KS, c) : zp);
+        for (int c = 0; c < 4; ++c) f[c] = *(kk + KS < khi ? src(kk + KS, c) : zp);
       if (!GATHER && 4 * kk + 3 < L) {
 #pragma unroll
         for (int m = 0; m < M; ++m) {
@@ -869,7 +872,7 @@ __global__ __launch_bounds__(64 * KS) void k_gemv_rows(PassArgs a) {
       }
     }
   }
-  if constexpr (KS > KR) {  // the upper waves' sums go to the lower ones first
+  if constexpr (KS > KH) {  // the upper waves' sums go to the lower ones first
     if (kw >= KR)
 #pragma unroll
       for (int m = 0; m < M; ++m) {
@@ -884,7 +887,7 @@ __global__ __launch_bounds__(64 * KS) void k_gemv_rows(PassArgs a) {
         yi[m] += red[((kw * M + m) * 2 + 1) * 64 + lane];
       }
   }
-  if (kw < KR)
+  if (kw < KH)
 #pragma unroll
     for (int m = 0; m < M; ++m) {
       red[((kw * M + m) * 2 + 0) * 64 + lane] = yr[m];
@@ -897,8 +900,13 @@ __global__ __launch_bounds__(64 * KS) void k_gemv_rows(PassArgs a) {
     if (m >= nm || arow >= L) continue;
     double sr = 0.0, si = 0.0;
     for (int w = 0; w < KR; ++w) {
-      sr += red[((w * M + m) * 2 + 0) * 64 + ln];
-      si += red[((w * M + m) * 2 + 1) * 64 + ln];
+      double vr = red[((w * M + m) * 2 + 0) * 64 + ln], vi = red[((w * M + m) * 2 + 1) * 64 + ln];
+      if constexpr (KH > KR) {
+        vr += red[(((w + KR) * M + m) * 2 + 0) * 64 + ln];
+        vi += red[(((w + KR) * M + m) * 2 + 1) * 64 + ln];
+      }
+      sr += vr;
+      si += vi;
     }
     const int p = (ORB ? a.orbit[(int64_t)t.f * kOrbitStride + 1 + m] : t.r0) + arow;
     if (FMT != PF_F64) {
