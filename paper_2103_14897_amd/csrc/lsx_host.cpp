@@ -2023,7 +2023,9 @@ static lsx_status choose_tiles(lsx_plan* pl, lsx_state* st) {
         a.u = c.u;
         // two timed passes (enough for passes of a millisecond or more), then, for shorter
         // passes, at least five and about 0.5 ms of them (at most a hundred): launch jitter is
-        // comparable to a few-microsecond pass
+        // comparable to a few-microsecond pass.  1 ms of them for a single state, whose shapes no
+        // step-cycle tuning corrects.
+        const float span_ms = W == 1 ? 1.0f : 0.5f;
         auto time_reps = [&](int reps, float& per) {
           hipError_t e = hipEventRecord(e0, nullptr);
           for (int r = 0; r < reps && e == hipSuccess; ++r)
@@ -2039,7 +2041,7 @@ static lsx_status choose_tiles(lsx_plan* pl, lsx_state* st) {
         if (he == hipSuccess) he = time_reps(2, ms);
         // a shape this far behind the two best so far is not timed further
         const bool behind = second >= 0.f && ms > 1.2f * second + 5e-3f;
-        if (he == hipSuccess && ms < 1.0f && !behind) he = time_reps(std::min(100, std::max(5, (int)(0.5f / std::max(ms, 1e-3f)))), ms);
+        if (he == hipSuccess && ms < 1.0f && !behind) he = time_reps(std::min(100, std::max(5, (int)(span_ms / std::max(ms, 1e-3f)))), ms);
         if (he != hipSuccess) {
           err = fail(LSX_E_HIP, std::string("autotune: ") + hipGetErrorString(he));
           break;
