@@ -402,9 +402,11 @@ lsx_status lsx_state_destroy(lsx_state* st);
  * one call are merged, F1(tau/2) F1(tau/2) = F1(tau), and so are the adjacent F1 sub-steps
  * of the Yoshida scheme; Crank-Nicolson steps are applied unmerged).  nsteps >= 0.
  * Stream-ordered.  Small systems run all passes of a call in one launch, one workgroup per
- * wavepacket: at most 2048 rows and 32 distinct passes (so not long Crank-Nicolson calls), W = 1 or
- * LSX_FP64, and either at most 256 rows with bands of at most 24 columns and a two-pass step body,
- * or at most 48 KB of propagator entries per pass (per 256 wavepackets).  The tile shapes below do
+ * wavepacket: at most 512 rows and 32 distinct passes (so not long Crank-Nicolson calls), W = 1 or
+ * LSX_FP64, and either at most 256 rows with bands of at most 24 columns, a two-pass step body and W
+ * <= 1024, or at most 48 KB of propagator entries in any pass (per 256 wavepackets) and 4096 entries in
+ * the mean one.  LSX_FP64 and LSX_MIX_FP32 calls of few passes are left out: at least one pass for every
+ * 640 entries of the mean pass (times two beyond 256 rows, per 256 wavepackets).  The tile shapes below do
  * not enter there.  Elsewhere, where the passes are launch-bound (every layer's tuned pass at most
  * 20 us) and a call repeats the step body often enough, the library captures its passes
  * once into HIP graphs and replays them: graphs of about 512 passes for the bulk of the

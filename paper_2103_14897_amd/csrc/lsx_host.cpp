@@ -1030,9 +1030,9 @@ static lsx_status block_jacobi(hipStream_t s, const std::vector<int32_t>& sel, c
   return LSX_OK;
 }
 
-// Resident steps hold two copies of a column in LDS: 2048 rows are 64 KB.  kResidentBytes ends before
-// that (512 rows, 1536 where only the diagonal blocks of a mixed path are multiplied).
-static constexpr int64_t kResidentMaxRows = 2048;
+// Resident steps hold two copies of a column in LDS and sweep it in 256 rows (four lanes a row): at most
+// two sweeps, from three on a launch over the whole chip is as fast (see use_resident).
+static constexpr int64_t kResidentMaxRows = 512;
 // Row table of the resident steps and the propagator bytes a pass reads per column.
 static lsx_status resident_rows(lsx_plan* pl, int layer, hipStream_t s) {
   LayerDev& ld = pl->L[layer - 1];
@@ -2463,25 +2463,40 @@ void step_sequence(int scheme, int nl, int64_t nsteps, std::vector<PassSpec>& he
 }  // namespace
 
 // Whether a call's passes run as one resident launch (lsx_resident.hip): a single state in any
-// precision or FP64 columns (whose arithmetic the resident passes share), a column that fits LDS,
-// and either a body whose two passes fit the registers (`pair`), or few enough propagator bytes per
-// pass that one workgroup reads them once per column sooner than a launch over the whole chip
-// ends.  Microseconds per Strang step, launches / resident, FP64 chains of W = 1: N = 53 (pair) 5.6 /
-// 1.05, N = 155 (pair) 5.4 / 1.5, three layers N = 127 (11 KB) 9.7 / 4.8, without pairs 36 KB 5.5 / 3.5,
-// 50 KB 5.8 / 4.5, 122 KB 5.9 / 8.7; W = 256 as W = 1 (one workgroup per CU).
-static constexpr int64_t kResidentBytes = 49152;
+// precision or FP64 columns (whose arithmetic the resident passes share), a column of at most two
+// sweeps, and either a body whose two passes fit the registers (`pair`), or few enough propagator
+// bytes in any pass and entries in the mean pass that one workgroup reads them once per column sooner
+// than a launch over the whole chip ends.  Microseconds per Strang step, launches / resident, W = 1: N = 53 (pair) 5.6 / 1.05, N =
+// 155 (pair) 5.4 / 1.5, three layers N = 127 9.7 / 4.8; without pairs three layers N = 343 (44 KB, 2744
+// entries) in FP64 10.7 / 9.0 and FP32 11.5 / 10.2, N = 441 (5292 entries) FP32 11.6 / 12.8, chain N = 265
+// (4612) FP32 5.6 / 5.6, N = 339 (6056) FP32 5.7 / 7.2; three sweeps of few entries (N = 513, 2052) 6.1 / 5.9,
+// four (N = 775, 3100) 6.1 / 7.8.
+// W = 256 runs as W = 1 (one workgroup per CU), and more wavepackets in rounds of 256.
+// A short call is mostly the first read of each pass's entries, by a few lanes of one workgroup: it is
+// resident from kResidentPerPass entries (times sweeps and rounds) a pass.  Whole calls of one and two
+// Strang steps, launches / resident: N = 155, W = 64 (2648 entries) 9.4 / 8.4 and 15.5 / 11.4; N = 229, W =
+// 256 (3988) 9.9 / 12.1 and 16.5 / 17.4, three steps 23.1 / 18.8; N = 229, W = 512 19.5 / 32.4, five steps 43 /
+// 41.  Not so BF16x3, whose launched passes take 3.4 us: one Lie step N = 123 8.3 / 7.0.
+static constexpr int64_t kResidentBytes = 49152, kResidentEntries = 4096, kResidentPerPass = 640;
 static constexpr int kResidentPairRows = 256, kResidentPairMaxW = 1024;
 static bool resident_pair(const lsx_plan* pl, size_t nbody) {
   bool pair = pl->fmt != PF_BF16X3 && nbody == 2 && pl->sys->N <= kResidentPairRows;
   for (int j = 0; j < pl->sys->nl; ++j) pair = pair && pl->L[j].band_steps <= kResidentU;
   return pair;
 }
-static bool use_resident(const lsx_plan* pl, const lsx_state* st, size_t npass, size_t nbody) {
+// npass: distinct passes of the call; total: passes it runs; nbody: passes of the repeated body
+static bool use_resident(const lsx_plan* pl, const lsx_state* st, size_t npass, int64_t total, size_t nbody) {
   if (pl->sys->N > kResidentMaxRows || (st->W > 1 && pl->fmt != PF_F64) || npass > (size_t)kResidentPasses) return false;
+  int64_t most = 0, sum = 0;
+  for (int j = 0; j < pl->sys->nl; ++j) {
+    most = std::max(most, pl->L[j].band_bytes);
+    sum += pl->L[j].band_bytes;
+  }
+  const int64_t entries = sum / pl->sys->nl / (pl->fmt == PF_F64 ? 16 : pl->fmt == PF_F32 ? 8 : 12);
+  const int64_t rounds = (st->W + 255) / 256, sweeps = (pl->sys->N + 255) / 256;
+  if (pl->fmt != PF_BF16X3 && entries * sweeps * rounds > kResidentPerPass * total) return false;
   if (resident_pair(pl, nbody)) return st->W <= kResidentPairMaxW;
-  int64_t most = 0;
-  for (int j = 0; j < pl->sys->nl; ++j) most = std::max(most, pl->L[j].band_bytes);
-  return most * ((st->W + 255) / 256) <= kResidentBytes;
+  return entries <= kResidentEntries && most * rounds <= kResidentBytes;
 }
 
 // The sequence head, body x reps, tail as resident launches of at most kResidentSpan passes each (a
@@ -2532,7 +2547,8 @@ extern "C" lsx_status lsx_step(lsx_plan* pl, lsx_state* st, int64_t nsteps, void
   int64_t reps = 0;
   step_sequence(pl->scheme, pl->sys->nl, nsteps, head, body, tail, reps);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (use_resident(pl, st, head.size() + body.size() + tail.size(), body.size()))
+  const int64_t total = (int64_t)head.size() + (int64_t)body.size() * reps + (int64_t)tail.size();
+  if (use_resident(pl, st, head.size() + body.size() + tail.size(), total, body.size()))
     return resident_steps(pl, st, s, head, body, tail, reps);
   // body repetitions per captured graph (the ladder): about graph_passes() passes for the bulk
   // of the call, then halved sizes down to about graph_min_passes() passes for its remainder,

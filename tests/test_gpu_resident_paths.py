@@ -2,8 +2,8 @@
 its two arrays after an odd number of ordinary passes and keeps them in a resident call, which works
 in place.  Each system's steps against the same sub-steps as separate calls (lsx_fibre_pass and
 lsx_phase, ordinary launches): several sweeps of the workgroup over the rows (more than 256), bands
-longer than the entries a lane loads together, BF16x3 bands of several chunks, and the sizes next to
-the byte rule that are not resident."""
+longer than the entries a lane loads together, BF16x3 bands of several chunks, and calls next to the
+rules that are not resident."""
 import numpy as np
 import pytest
 
@@ -31,26 +31,33 @@ def chain(Ec, v=1.0):
 
 
 # band_tol: None the default, < 0 dense products, 1e-4: above every off-diagonal entry (tau |v| = 2e-5),
-# so that of a mixed path's blocks only the chunk of four columns at the diagonal is multiplied and 48 KB
-# hold the bands of 1536 rows
-@pytest.mark.parametrize("make,N,W,precision,band_tol,resident", [
-    (lambda: chain(1000.0), 265, 1, "mix_fp32", None, True),           # two sweeps, the second of 9 rows
-    (lambda: chain(1300.0), 339, 1, "mix_fp32", None, True),
-    (lambda: chain(1500.0), 389, 1, "mix_fp32", None, False),
-    (lambda: chain(1500.0), 389, 1, "fp64", None, False),
-    (lambda: blocks(3, 3, 3), 343, 1, "fp64", None, True),             # two sweeps, fibres of seven rows
-    (lambda: blocks(3, 3, 3), 343, 3, "fp64", None, True),
-    (lambda: blocks(3, 3, 4), 441, 1, "mix_fp32", None, True),
-    (lambda: chain(5000.0, 0.01), 1281, 1, "mix_fp32", 1e-4, True),    # six sweeps
-    (lambda: blocks(20, 1), 123, 1, "mix_fp32", -1.0, True),           # 41 columns: eleven k-steps
-    (lambda: blocks(20, 0), 41, 2, "fp64", -1.0, True),
-    (lambda: blocks(16, 0), 33, 1, "mix_bf16x3", -1.0, True),          # two chunks, the second of one column
-    (lambda: blocks(20, 0), 41, 1, "mix_bf16x3", -1.0, True),
-    (lambda: blocks(20, 1), 123, 1, "mix_bf16x3", -1.0, False),
+# so that of a mixed path's blocks only the chunk of four columns at the diagonal is multiplied.
+# start: the fewest of 1, 2 or 5 steps that are resident (a call of few passes is not where its entries
+# are many), None: none is
+@pytest.mark.parametrize("make,N,W,precision,band_tol,start", [
+    (lambda: chain(150.0), 41, 1, "fp64", None, 1),                 # bodies of two passes in registers
+    (lambda: chain(600.0), 155, 1, "fp64", None, 2),
+    (lambda: chain(600.0), 155, 1, "mix_fp32", None, 2),
+    (lambda: chain(600.0), 155, 300, "fp64", None, 5),              # two rounds of workgroups
+    (lambda: chain(900.0), 229, 3, "fp64", None, 5),
+    (lambda: chain(600.0), 155, 1100, "fp64", None, None),
+    (lambda: chain(1000.0), 265, 1, "mix_fp32", None, None),        # more than 4096 entries
+    (lambda: chain(1500.0), 389, 1, "fp64", None, None),
+    (lambda: chain(1000.0, 0.01), 265, 1, "mix_fp32", 1e-4, 2),     # two sweeps, the second of 9 rows
+    (lambda: chain(2000.0, 0.01), 513, 1, "mix_fp32", 1e-4, None),  # three
+    (lambda: blocks(3, 3, 3), 343, 1, "fp64", None, 2),             # two sweeps, fibres of seven rows
+    (lambda: blocks(3, 3, 3), 343, 1, "mix_fp32", None, 2),
+    (lambda: blocks(3, 3, 3), 343, 3, "fp64", None, 2),
+    (lambda: blocks(3, 3, 4), 441, 1, "mix_fp32", None, None),
+    (lambda: blocks(20, 1), 123, 1, "mix_fp32", -1.0, 5),           # 44 and 16 columns: eleven k-steps
+    (lambda: blocks(20, 0), 41, 2, "fp64", -1.0, 1),
+    (lambda: blocks(16, 0), 33, 1, "mix_bf16x3", -1.0, 1),          # two chunks, the second of one column
+    (lambda: blocks(20, 0), 41, 1, "mix_bf16x3", -1.0, 1),
+    (lambda: blocks(20, 1), 123, 1, "mix_bf16x3", -1.0, None),
 ])
-def test_resident_calls(make, N, W, precision, band_tol, resident):
+def test_resident_calls(make, N, W, precision, band_tol, start):
     S = make()
-    print(f"[case] N={S.N} W={W} {precision} band_tol={band_tol} resident={resident}", flush=True)
+    print(f"[case] N={S.N} W={W} {precision} band_tol={band_tol} start={start}", flush=True)
     try:
         assert S.N == N
         strang, lie = (STRANG3, LIE3) if S.nlayers == 3 else (STRANG, LIE)
@@ -65,7 +72,7 @@ def test_resident_calls(make, N, W, precision, band_tol, resident):
                     at = whole.device_ptr()
                     whole.step(n)
                     if scheme == "strang":  # 2 n + 1 passes, 4 n + 1 with three layers
-                        assert (whole.device_ptr() == at) == resident
+                        assert (whole.device_ptr() == at) == (start is not None and n >= start)
                     for _ in range(n):
                         for layer, half, ph in seq:
                             parts.fibre_pass(layer, half)
