@@ -2265,9 +2265,12 @@ extern "C" lsx_status lsx_state_destroy(lsx_state* st) {
 // applied in that pass's epilogue.
 namespace {
 // A single state of at least this many rows is put into a pass's order first where it is in another
-// one (a call's first pass): inside the pass, every tile that reads a row reads it by itself through
-// the table.  One Strang step of the twisted bilayer, through the table / reordered first: N = 398821
-// 147 / 101 us, 85261 61 / 40, 36937 27.7 / 24.7, 9061 13.9 / 15.0.
+// one (a call's first pass) and the pass's tiles read it through the table too slowly: those of several
+// fibres with one propagator, and the eight-row reads of BF16x3.  Tiles of single fibres in FP64 and FP32
+// hide the table behind their other loads.  One Strang step of the twisted bilayer, through the table /
+// reordered first, us: tiles of several fibres FP32 N = 398821 147 / 101, 80461 61 / 39, FP64 N = 122965 111 / 70;
+// BF16x3 N = 58837 45 / 37, 34309 29 / 26, 19081 21 / 20 (a Lie step of an owned state 14 / 15); single fibres
+// FP32 N = 49909 24 / 26, FP64 35 / 34 (a Lie step 24 / 26).
 static constexpr int64_t kGatherMinRows = 32768;
 
 struct Runner {
@@ -2298,7 +2301,8 @@ struct Runner {
     if (phase_half >= 0 && pl->kappa != 0.0 && !pl->phase[phase_half].p)
       return fail(LSX_E_INVALID, "plan holds no phase table for this slot");
     const int outlay = next;  // 0: canonical order
-    if (st->W == 1 && pl->sys->N >= kGatherMinRows && table(layer, lay)) {
+    if (st->W == 1 && pl->sys->N >= kGatherMinRows && (st->nb[layer - 1] == kOrbitNB || pl->fmt == PF_BF16X3) &&
+        table(layer, lay)) {
       const int to = target(false);
       LSX_HIP_TRY(launch_gather_rows(s, pl->sys->N, table(layer, lay), st->buf[cur], st->buf[to]));
       cur = to;
