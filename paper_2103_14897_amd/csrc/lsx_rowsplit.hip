@@ -176,7 +176,7 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f32m(PassArgs a) {
 // registers its predecessor just left (a whole chunk of products ahead of its use, and no second
 // set of registers), and the chunks a wave only stages are separate loops, without a branch
 // around the products (which copied every accumulator).  Five vector instructions per 24
-// products, 92 registers (NB = 2): five waves per SIMD.
+// products, 94 registers (NB = 2): five waves per SIMD.
 // Twisted bilayer, N = 398821, W = 128, tau = 5e-3, layer 1 / 2: 1688 / 1515 us a pass, 59 TF of
 // matrix work; the fastest K-split shape takes 2030 / 1800, as did this kernel when it formed the
 // sums in every wave with addresses in vector registers (1970 / 1790).  Measured slower: MS = 2
@@ -312,7 +312,7 @@ __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_f64m(PassArgs a) {
 // Twisted bilayer, N = 398821, W = 128, tau = 1e-3, 2 column blocks and 8 waves, layer 1 / 2: 718 /
 // 651 us a pass with planes for two chunks in registers (124), their addresses in vector
 // registers and two-byte staging stores into padded columns (28% of the cycles lost to bank
-// conflicts); 690 / 624 now, with 100 registers; the trilayer's best shape 564 to 505 us.
+// conflicts); 690 / 624 now, with 94 registers; the trilayer's best shape 564 to 505 us.
 template <int NB, int MS, bool GATHER>
 __global__ LSX_MFMA_BOUNDS(64 * MS, true) void k_pass_bf16m(PassArgs a) {
   constexpr int CW = 16 * NB;
