@@ -3578,19 +3578,20 @@ lsx_status apply_phase(lsx_plan* pl, lsx_state* st, const double2* ph, hipStream
 // tiles of a whole pass.  Each wave's FP32 sums cover other k-steps and the weights multiply their
 // rounding (two splits differ by 1e-8 of the state), so the split does not follow the state's timed
 // shape, which differs from one state to the next near a tie.  The lines lie where the fastest length
-// split of a whole FP32 pass changed when shapes were timed by states of 265 sizes (twisted bilayer,
-// kappa = 1, N = 2137 to 341053, W = 8 to 128): both layers split alike at 161 of the 181 sizes where
-// all states of a size agreed.  Four waves up to 8 tiles a CU, 16 where the column blocks go in pairs,
-// 20 for one or two column blocks (long fibres); two up to 72, then one; past 256 a CU shapes of two waves
-// were picked again.  BF16x3 chunks are eight k-steps long: four waves below two tiles a CU, else two.
-// A pinned or forced shape is followed (two waves for a row split).
+// split of a whole FP32 pass changed when shapes were timed by three states each of 740 sizes on two
+// cards (twisted bilayer, kappa = 1, N = 2377 to 341053, W = 8 to 128): both layers split alike at 472 of the
+// 523 sizes where the three agreed, and no line through tiles and columns did better on both cards.  Four
+// waves up to 8 tiles a CU, 20 for one or two column blocks (long fibres); two up to 72, then one; two again
+// past 256 a CU, and past 100 for three column blocks, of which a shape of two leaves one half empty.
+// BF16x3 chunks are eight k-steps long: four waves below two tiles a CU, else two.  A pinned or forced shape is
+// followed (two waves for a row split).
 int slot_waves(const lsx_sampler* sm, int j) {
   const lsx_state* st = sm->st;
   if (!(st->tuned_us[j] > 0.f)) return st->ks[j] > 0 ? st->ks[j] : 2;
   const int64_t wt = (st->W + 15) / 16, per_cu = sm->ntiles[j] * wt / 256;
   if (sm->pl->fmt == PF_BF16X3) return per_cu < 2 ? 4 : 2;
-  if (per_cu < (wt <= 2 ? 20 : wt % 2 ? 8 : 16)) return 4;
-  return per_cu < 72 || per_cu >= 256 ? 2 : 1;
+  if (per_cu < (wt <= 2 ? 20 : 8)) return 4;
+  return per_cu < 72 || per_cu >= (wt == 3 ? 100 : 256) ? 2 : 1;
 }
 
 // One sampled sub-step of `layer` with propagators `half`, uniforms u [W][ustride].  pend: phase the
