@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256) void k_si_step(Sweep sweep, int W, int CW, dou
   const int r0 = sweep.start[xcd], r1 = sweep.start[xcd + 1];
   const int rpi = 256 / CW;  // rows per workgroup iteration
   const int tr = threadIdx.x / CW, tc = threadIdx.x - tr * CW;
-  for (int cb = 0; cb < W; cb += CW) {
+  for (int cb = (int)blockIdx.y * CW; cb < W; cb += (int)gridDim.y * CW) {
     const int w = cb + tc;
     if (w >= W) continue;
     for (int k = r0 + lb * rpi + tr; k < r1; k += G * rpi) {
@@ -458,7 +458,10 @@ hipError_t launch_si_step(hipStream_t s, const Sweep& rows, int W, double tau, c
   int64_t rows_per_xcd = 0;
   for (int x = 0; x < 8; ++x) rows_per_xcd = std::max<int64_t>(rows_per_xcd, sweep.start[x + 1] - sweep.start[x]);
   const int64_t G = std::min<int64_t>(256, std::max<int64_t>(1, (rows_per_xcd * CW + 255) / 256));
-  const dim3 grid((unsigned)(8 * G));
+  // few rows: the column blocks go to workgroups of their own, up to one a CU (random batch step of N = 79,
+  // W = 128: 28 to 11 us); the elements are the same
+  const int64_t ny = std::max<int64_t>(1, std::min<int64_t>((W + CW - 1) / CW, 256 / (8 * G)));
+  const dim3 grid((unsigned)(8 * G), (unsigned)ny);
   if (nv1 == 2 && nv2 == 2)
     hipLaunchKernelGGL((k_si_step<2, 2>), grid, dim3(256), 0, s, sweep, W, CW, tau, K2, nv1, nbr1, v1, wt1, fid1, nv2,
                        nbr2, v2, wt2, fid2, X, Y, zero);

@@ -25,7 +25,23 @@ def twisted():
 @pytest.mark.parametrize("W", [9, 13, 17, 31, 33, 48, 63, 248, 256])
 def test_wide_states_equal_narrow_ones(twisted, W, monkeypatch):
     monkeypatch.setenv("LSX_AUTOTUNE", "0")
-    S, P = twisted
+    compare(*twisted, W)
+
+
+# few rows, whose column blocks are on workgroups of their own: one block, all at once, and more blocks (38
+# and 13) than workgroups a row group has (32 and 8)
+@pytest.mark.parametrize("Ec,W", [(300.0, 7), (300.0, 100), (300.0, 300), (3000.0, 100)])
+def test_small_systems(Ec, W):
+    S = lsx.System.from_spec(wl.chain_system(Ec))
+    P = lsx.Plan(S, 5e-3, "lie", 1.0, "fp64")
+    try:
+        compare(S, P, W)
+    finally:
+        P.destroy()
+        S.destroy()
+
+
+def compare(S, P, W):
     print(f"[case] semi-implicit N={S.N} W={W}", flush=True)
     cols = sorted({0, 7, 8, W // 2, W - 2, W - 1} & set(range(W)))
     g = torch.Generator(device="cuda").manual_seed(W)
