@@ -25,7 +25,7 @@ def twisted():
 @pytest.mark.parametrize("W", [9, 13, 17, 31, 33, 48, 63, 248, 256])
 def test_wide_states_equal_narrow_ones(twisted, W, monkeypatch):
     monkeypatch.setenv("LSX_AUTOTUNE", "0")
-    compare(*twisted, W)
+    compare(*twisted, W, (7, 11))
 
 
 # few rows, whose column blocks are on workgroups of their own: one block, all at once, and more blocks (38
@@ -35,19 +35,18 @@ def test_small_systems(Ec, W):
     S = lsx.System.from_spec(wl.chain_system(Ec))
     P = lsx.Plan(S, 5e-3, "lie", 1.0, "fp64")
     try:
-        compare(S, P, W)
+        compare(S, P, W, (3, 5))
     finally:
         P.destroy()
         S.destroy()
 
 
-def compare(S, P, W):
+def compare(S, P, W, p):
     print(f"[case] semi-implicit N={S.N} W={W}", flush=True)
     cols = sorted({0, 7, 8, W // 2, W - 2, W - 1} & set(range(W)))
     g = torch.Generator(device="cuda").manual_seed(W)
     c = torch.view_as_complex(torch.randn((S.N, W, 2), dtype=torch.float64, device="cuda", generator=g))
     d = c[:, cols].contiguous()
-    p = (7, 11)
     u = torch.as_tensor(wl.uniforms((1, 2, W, max(p)), seed=1), device="cuda")
     wide, narrow = lsx.State(P, W, dev_ptr=c.data_ptr()), lsx.State(P, len(cols), dev_ptr=d.data_ptr())
     sw, sn = lsx.Sampler(wide, *p), lsx.Sampler(narrow, *p)
